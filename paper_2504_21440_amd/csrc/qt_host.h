@@ -93,7 +93,12 @@ struct Liouv {
     // time dependence (CSR form): column tags 1..nterms select the coefficient of each entry
     int32_t nterms = 0;
     void *coefs = nullptr;  // device: CoefDev[nterms] followed by their sample tables
-    // host copies needed by the Monte-Carlo path and by the server footprint estimate
+    // resident solver (kernels_res.hip): the most generator entries of an element (0: not eligible) and,
+    // in the dense form, the upper-triangle ELL a plan or server uploads (res_build_ell)
+    int32_t res_w = 0;
+    bool res_band = false;
+    std::vector<int32_t> res_col;
+    std::vector<double2> res_val;
 };
 
 // Time-dependent coefficients: validation of a qt_coef (QT_COEF_NONE accepted when allow_none) and

@@ -17,6 +17,7 @@
 #include "qt_csr.h"
 #include "qt_dense.h"
 #include "qt_host.h"
+#include "qt_res.h"
 #include "qt_tune.h"
 #include "qt_coef.h"
 
@@ -27,6 +28,7 @@ struct MeProb {
     int32_t d = 0, nt = 0, ne = 0;
     bool dense = false;
     int32_t slot = -1;  // index inside its group
+    int32_t res = -1;   // index among the resident problems (kernels_res.hip), -1: not one
     size_t o_rho0 = 0, o_tlist = 0, o_eptr = 0, o_ecol = 0, o_eval = 0, o_evidx = 0, o_expect = 0;
     size_t o_vec = 0;  // state vectors
     size_t o_part = 0;
@@ -82,6 +84,17 @@ struct qt_me_plan {
         int32_t np, start, count;
     };
     std::vector<Bucket> buckets;  // dense problems grouped by padded size, largest first
+    std::vector<Bucket> mfma;     // the same without the resident ones (positions in the order list)
+    size_t o_dorder2 = 0;
+    // Resident problems: constant generators of few entries per element with a Hermitian initial
+    // state, whatever their form.  A run integrates each in one workgroup; they keep their place in the
+    // CSR and dense groups, whose shapes, tables and timings cover every problem of the form.
+    int32_t nres = 0;
+    size_t o_rinst = 0, o_rctl = 0, o_rorder = 0;
+    qt::ResCtl *h_rctl = nullptr;  // pinned
+    std::vector<Bucket> rbuckets;  // np: kernel class
+    bool res_stale = false;        // the ELLs of dense-form problems have been overwritten
+    bool lanes_all = true;         // the lanes hold the resident problems too (timing)
     double last_ms = 0.0;
     bool counted = false;  // holds a reference on ctx
 };
@@ -109,6 +122,80 @@ static bool trace_lanes()
 }
 
 static size_t state_es(int32_t prec) { return prec == QT_F64 ? sizeof(double2) : sizeof(float2); }
+
+size_t res_ell_offset(int d, int prec)
+{
+    return (((size_t)2 * d * d + d) * state_es(prec) + 255) & ~size_t(255);
+}
+size_t res_ell_bytes(const Liouv &L) { return L.res_val.size() * (state_es(L.precision) + 4); }
+
+// The resident kernel takes a constant generator of few entries per element whose initial state is
+// exactly Hermitian (the dense form integrates the Hermitian part anyway); a dense-form problem's
+// ELL has to fit beside the state in the vectors the matrix-core solver would use.
+bool res_problem(const Liouv &L, bool dense, const double *rho0)
+{
+    if (L.res_w <= 0 || L.nterms > 0) return false;
+    const int32_t d = L.d;
+    if (dense) return res_ell_offset(d, L.precision) + res_ell_bytes(L) <=
+                      dense_state_vectors() * (size_t)dense_np(d) * dense_np(d) * state_es(L.precision);
+    for (int32_t i = 0; i < d; ++i)
+        for (int32_t j = i; j < d; ++j) {
+            const size_t a = 2 * ((size_t)i * d + j), b = 2 * ((size_t)j * d + i);
+            if (rho0[a] != rho0[b] || rho0[a + 1] != -rho0[b + 1]) return false;
+        }
+    return true;
+}
+
+// Fills a resident descriptor (vec: the problem's state vectors).
+void res_fill_inst(ResInst *g, const Liouv &L, bool dense, int nt, int ne, const void *rho0, void *vec,
+                   const double *tlist, const int32_t *eptr, const int32_t *evidx, const double2 *eval,
+                   double2 *expect, const qt_opts &opts, double steady_tol2)
+{
+    std::memset(g, 0, sizeof(*g));
+    g->d = L.d;
+    g->nt = nt;
+    g->ne = ne;
+    g->W = L.res_w;
+    g->use_h0 = opts.h0 > 0 ? 1 : 0;
+    g->renorm = L.precision == QT_MIXED ? 1 : 0;
+    g->atol = opts.abstol;
+    g->rtol = opts.reltol;
+    g->h0 = opts.h0;
+    g->max_steps = opts.max_steps;
+    g->steady_tol2 = steady_tol2;
+    if (dense) {
+        char *e = (char *)vec + res_ell_offset(L.d, L.precision);
+        g->val = e;
+        g->col = (const int32_t *)(e + L.res_val.size() * state_es(L.precision));
+    } else {
+        g->rowptr = L.rowptr;
+        g->col = L.col;
+        g->val = L.val;
+    }
+    g->rho0 = rho0;
+    g->vec = vec;
+    g->tlist = tlist;
+    g->eptr = eptr;
+    g->evidx = evidx;
+    g->eval = eval;
+    g->expect = expect;
+}
+
+// Requests the upload of a dense-form problem's ELL behind its state; `stage` holds the bytes until the
+// stream has been waited for.
+qt_status res_upload_ell(const Liouv &L, void *vec, std::vector<char> &stage, hipStream_t s)
+{
+    const size_t es = state_es(L.precision), nv = L.res_val.size();
+    stage.resize(res_ell_bytes(L));
+    if (es == 16) std::memcpy(stage.data(), L.res_val.data(), nv * es);
+    else
+        for (size_t q = 0; q < nv; ++q)
+            ((float2 *)stage.data())[q] = make_float2((float)L.res_val[q].x, (float)L.res_val[q].y);
+    std::memcpy(stage.data() + nv * es, L.res_col.data(), nv * 4);
+    QT_HIP(hipMemcpyAsync((char *)vec + res_ell_offset(L.d, L.precision), stage.data(), stage.size(),
+                          hipMemcpyHostToDevice, s));
+    return QT_OK;
+}
 
 static qt_status prep_problem(const qt_me_problem &p, int32_t prec, MeProb *m)
 {
@@ -165,6 +252,7 @@ static qt_status prep_problem(const qt_me_problem &p, int32_t prec, MeProb *m)
         float *f = (float *)m->rho0.data();
         for (size_t i = 0; i < 2 * n; ++i) f[i] = (float)r[i];
     }
+    m->res = res_problem(*p.L, m->dense, r.data()) ? 0 : -1;
     // e_ops as concatenated int32 CSR (instance-local offsets)
     m->eptr.assign((size_t)p.n_e * (d + 1), 0);
     m->ecol.clear();
@@ -238,7 +326,11 @@ static qt_status reset_lanes(qt_me_plan *P)
     for (auto &l : P->lanes) drop_graph(l);
     P->lanes.assign(1, qt_me_plan::Lane{});
     auto &l = P->lanes[0];
-    for (int32_t i = 0; i < P->ncsr; ++i) l.members.push_back(i);
+    // resident problems have no launches of their own in a run, only in the stage timing
+    for (auto &m : P->probs)
+        if (!m.dense && (P->lanes_all || m.res < 0)) l.members.push_back(m.slot);
+    l.listed = (int32_t)l.members.size() < P->ncsr;
+    l.done = l.members.empty();
     l.stream = P->ctx->stream;
     P->split = false;
     return layout_lanes(P);
@@ -256,10 +348,14 @@ static qt_status apply_shape(qt_me_plan *P, CsrShape sh)
 
 // Back to the single full lane if a run left the problems split or dropped; a lane that only
 // finished keeps its layout and graph.
-static qt_status restore_full(qt_me_plan *P)
+static qt_status restore_full(qt_me_plan *P, bool all)
 {
-    if (P->split) return reset_lanes(P);
-    for (auto &l : P->lanes) l.done = false;
+    all = all || P->nres == 0;
+    if (P->split || all != P->lanes_all) {
+        P->lanes_all = all;
+        return reset_lanes(P);
+    }
+    for (auto &l : P->lanes) l.done = l.members.empty();
     return QT_OK;
 }
 
@@ -341,6 +437,15 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
         P->o_dinst = A.reserve(sizeof(DenseInst) * P->ndense);
         P->o_dctl = A.reserve(sizeof(DenseCtl) * P->ndense);
         P->o_dorder = A.reserve(sizeof(int32_t) * P->ndense);
+        P->o_dorder2 = A.reserve(sizeof(int32_t) * P->ndense);
+    }
+    for (auto &m : P->probs)
+        if (m.res >= 0) m.res = P->nres++;
+    if (P->nres) {
+        P->o_rinst = A.reserve(sizeof(ResInst) * P->nres);
+        P->o_rctl = A.reserve(sizeof(ResCtl) * P->nres);
+        P->o_rorder = A.reserve(sizeof(int32_t) * P->nres);
+        P->lanes_all = false;
     }
     if (query) {
         *query = A.size;
@@ -359,6 +464,8 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
     for (auto &m : P->probs)
         if (!m.dense) P->csr_tend[m.slot] = m.tlist.back();
     std::vector<DenseInst> di(P->ndense);
+    std::vector<ResInst> ri(P->nres);
+    std::vector<std::vector<char>> ells(P->nres);
     for (auto &m : P->probs) {
         if ((st = upload(A.at(m.o_rho0), m.rho0.data(), m.rho0.size(), s))) break;
         if ((st = upload(A.at(m.o_tlist), m.tlist.data(), m.tlist.size() * 8, s))) break;
@@ -416,6 +523,33 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
                             (double2 *)A.at(m.o_expect), opts, P->prec);
             g.steady_tol2 = steady_tol * steady_tol;
         }
+        if (m.res >= 0) {
+            res_fill_inst(&ri[m.res], *m.L, m.dense, m.nt, m.ne, A.at(m.o_rho0), A.at(m.o_vec),
+                          (const double *)A.at(m.o_tlist), (const int32_t *)A.at(m.o_eptr),
+                          (const int32_t *)A.at(m.o_evidx), (const double2 *)A.at(m.o_eval),
+                          (double2 *)A.at(m.o_expect), opts, steady_tol * steady_tol);
+            if (m.dense && (st = res_upload_ell(*m.L, A.at(m.o_vec), ells[m.res], s))) break;
+        }
+    }
+    std::vector<int32_t> rorder(P->nres);
+    if (!st && P->nres) {
+        // by class, the largest problems of a class first
+        std::vector<int32_t> cls(P->nres), dim(P->nres);
+        for (auto &m : P->probs)
+            if (m.res >= 0) cls[m.res] = res_class(m.d, m.L->res_w, m.L->res_band, P->prec), dim[m.res] = m.d;
+        for (int32_t k = 0; k < P->nres; ++k) rorder[k] = k;
+        std::stable_sort(rorder.begin(), rorder.end(), [&](int32_t a, int32_t b) {
+            return cls[a] != cls[b] ? cls[a] > cls[b] : dim[a] > dim[b];
+        });
+        for (int32_t k = 0; k < P->nres; ++k) {
+            if (P->rbuckets.empty() || P->rbuckets.back().np != cls[rorder[k]])
+                P->rbuckets.push_back({cls[rorder[k]], k, 0});
+            P->rbuckets.back().count++;
+        }
+        if ((st = upload(A.at(P->o_rinst), ri.data(), sizeof(ResInst) * P->nres, s)) == QT_OK)
+            st = upload(A.at(P->o_rorder), rorder.data(), 4 * rorder.size(), s);
+        if (!st && hipHostMalloc((void **)&P->h_rctl, sizeof(ResCtl) * P->nres, hipHostMallocDefault) != hipSuccess)
+            st = set_error(QT_ENOMEM, "pinned host buffer");
     }
     if (!st && P->ncsr) {
         const double mean_row = rows_tot ? (double)nnz_tot / rows_tot : 8.0;
@@ -429,9 +563,10 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
             if (e) st = set_error(QT_ENOMEM, "pinned host buffer");
         }
     }
+    std::vector<int32_t> order, order2;  // alive until the uploads are waited for
     if (!st && P->ndense) {
         // largest problems first: the hardware dispatches workgroups in this order
-        std::vector<int32_t> order(P->ndense);
+        order.resize(P->ndense);
         for (int32_t i = 0; i < P->ndense; ++i) order[i] = i;
         std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return di[a].d > di[b].d; });
         for (int32_t k = 0; k < P->ndense; ++k) {
@@ -443,8 +578,20 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
             if (P->buckets.empty() || P->buckets.back().np != np) P->buckets.push_back({np, k, 0});
             P->buckets.back().count++;
         }
-        if (!st && (st = upload(A.at(P->o_dinst), di.data(), sizeof(DenseInst) * P->ndense, s)) == QT_OK)
-            st = upload(A.at(P->o_dorder), order.data(), 4 * order.size(), s);
+        // the problems the matrix-core kernel runs: those without a resident kernel
+        std::vector<char> res(P->ndense, 0);
+        for (auto &m : P->probs)
+            if (m.dense && m.res >= 0) res[m.slot] = 1;
+        for (int32_t k : order) {
+            if (res[k]) continue;
+            if (P->mfma.empty() || P->mfma.back().np != di[k].np)
+                P->mfma.push_back({di[k].np, (int32_t)order2.size(), 0});
+            P->mfma.back().count++;
+            order2.push_back(k);
+        }
+        if (!st && (st = upload(A.at(P->o_dinst), di.data(), sizeof(DenseInst) * P->ndense, s)) == QT_OK &&
+            (st = upload(A.at(P->o_dorder), order.data(), 4 * order.size(), s)) == QT_OK)
+            st = upload(A.at(P->o_dorder2), order2.data(), 4 * order2.size(), s);
         if (!st) {
             hipError_t e = hipHostMalloc((void **)&P->h_dctl, sizeof(DenseCtl) * P->ndense, hipHostMallocDefault);
             if (e) st = set_error(QT_ENOMEM, "pinned host buffer");
@@ -519,16 +666,43 @@ static qt_status capture_graph(qt_me_plan *P, int k = 0)
     return QT_OK;
 }
 
-static void launch_dense_buckets(qt_me_plan *P, int max_steps_launch, hipStream_t single)
+static void launch_dense_buckets(qt_me_plan *P, int max_steps_launch, hipStream_t single, bool all)
 {
     const bool f64 = P->prec == QT_F64;
-    for (size_t b = 0; b < P->buckets.size(); ++b) {
-        const auto &bk = P->buckets[b];
+    const auto &bks = all ? P->buckets : P->mfma;
+    const int32_t *order = (const int32_t *)P->arena.at(all ? P->o_dorder : P->o_dorder2);
+    for (size_t b = 0; b < bks.size(); ++b) {
+        const auto &bk = bks[b];
         hipStream_t bs = single ? single : P->ctx->pool[b % Ctx::NPOOL];
         dense_launch_bucket(bk.np, f64, dense_choose_config(bk.np, P->prec), (const DenseInst *)P->arena.at(P->o_dinst),
-                            (DenseCtl *)P->arena.at(P->o_dctl), (const int32_t *)P->arena.at(P->o_dorder) + bk.start,
-                            bk.count, max_steps_launch, /*reset=*/1, bs);
+                            (DenseCtl *)P->arena.at(P->o_dctl), order + bk.start, bk.count, max_steps_launch,
+                            /*reset=*/1, bs);
     }
+}
+
+// Every resident problem from its initial state to its last save time: one launch per kernel class, on
+// `single` or spread over the pool streams behind the matrix-core buckets.
+static qt_status launch_resident(qt_me_plan *P, hipStream_t single)
+{
+    if (P->res_stale) {
+        std::vector<char> stage;
+        for (auto &m : P->probs)
+            if (m.res >= 0 && m.dense) {
+                qt_status st = res_upload_ell(*m.L, P->arena.at(m.o_vec), stage, P->ctx->stream);
+                if (st) return st;
+                QT_HIP(hipStreamSynchronize(P->ctx->stream));
+            }
+        P->res_stale = false;
+    }
+    for (size_t b = 0; b < P->rbuckets.size(); ++b) {
+        const auto &bk = P->rbuckets[b];
+        hipStream_t bs = single ? single : P->ctx->pool[(P->mfma.size() + b) % Ctx::NPOOL];
+        qt_status st = res_launch(bk.np, P->prec == QT_F64, (const ResInst *)P->arena.at(P->o_rinst),
+                                  (ResCtl *)P->arena.at(P->o_rctl),
+                                  (const int32_t *)P->arena.at(P->o_rorder) + bk.start, bk.count, -1, 1, bs);
+        if (st) return st;
+    }
+    return QT_OK;
 }
 
 qt_status me_plan_run(qt_me_plan *P)
@@ -536,20 +710,29 @@ qt_status me_plan_run(qt_me_plan *P)
     Ctx *ctx = P->ctx;
     QT_HIP(hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
-    const bool f64 = P->prec == QT_F64;
     auto t0 = std::chrono::steady_clock::now();
-    // dense buckets run on the auxiliary streams, overlapping each other and the CSR group
+    int32_t ndres = 0;
+    for (auto &m : P->probs) ndres += m.dense && m.res >= 0;
+    const int32_t nmfma = P->ndense - ndres, nstaged = P->ncsr - (P->nres - ndres);
+    // matrix-core buckets and resident classes run on the auxiliary streams, overlapping each other and
+    // the staged CSR group; one resident class alone runs on the context's stream
     hipEvent_t ev_start = nullptr;
-    if (P->ndense) {
+    const bool lone = nmfma == 0 && nstaged == 0 && P->rbuckets.size() == 1;
+    if (lone) {
+        qt_status st = launch_resident(P, s);
+        if (st) return st;
+    } else if (nmfma || P->nres) {
         QT_HIP(hipEventCreateWithFlags(&ev_start, hipEventDisableTiming));
         QT_HIP(hipEventRecord(ev_start, s));
         for (int b = 0; b < Ctx::NPOOL; ++b) QT_HIP(hipStreamWaitEvent(ctx->pool[b], ev_start, 0));
-        launch_dense_buckets(P, -1, nullptr);
+        launch_dense_buckets(P, -1, nullptr, false);
         QT_HIP(hipGetLastError());
+        qt_status st = launch_resident(P, nullptr);
+        if (st) return st;
     }
     qt_status st = QT_OK;
-    if (P->ncsr) {
-        if ((st = restore_full(P))) return st;
+    if (nstaged) {
+        if ((st = restore_full(P, false))) return st;
         const CsrLaunch L = csr_args(P, 0);
         auto *cc = L.ctls;
         csr_launch_reset(L.insts, L.ctls, P->ncsr, L.f64, s);
@@ -669,10 +852,15 @@ qt_status me_plan_run(qt_me_plan *P)
             }
         }
     }
-    if (P->ndense) {
+    if (ev_start) {
         for (int b = 0; b < Ctx::NPOOL; ++b) QT_HIP(hipStreamSynchronize(ctx->pool[b]));
-        QT_HIP(hipMemcpy(P->h_dctl, P->arena.at(P->o_dctl), sizeof(DenseCtl) * P->ndense, hipMemcpyDeviceToHost));
         (void)hipEventDestroy(ev_start);
+    }
+    if (nmfma)
+        QT_HIP(hipMemcpy(P->h_dctl, P->arena.at(P->o_dctl), sizeof(DenseCtl) * P->ndense, hipMemcpyDeviceToHost));
+    if (P->nres) {
+        QT_HIP(hipMemcpyAsync(P->h_rctl, P->arena.at(P->o_rctl), sizeof(ResCtl) * P->nres, hipMemcpyDeviceToHost, s));
+        QT_HIP(hipStreamSynchronize(s));
     }
     P->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return QT_OK;
@@ -682,7 +870,7 @@ qt_status me_plan_run(qt_me_plan *P)
 static qt_status time_stage(qt_me_plan *P, int32_t reps, double *ms)
 {
     hipStream_t s = P->ctx->stream;
-    qt_status st = restore_full(P);
+    qt_status st = restore_full(P, true);
     if (st) return st;
     const CsrLaunch L = csr_args(P);
     hipEvent_t e0, e1;
@@ -737,6 +925,7 @@ qt_status me_plan_autotune(qt_me_plan *P, int32_t reps)
     if (P->ndense) {
         hipStream_t s = P->ctx->stream;
         const bool f64 = P->prec == QT_F64;
+        P->res_stale = P->nres > 0;  // the matrix-core kernel uses the vectors the ELLs are in
         for (const auto &bk : P->buckets) {
             int cand[8];
             const int nw = dense_waves_candidates(bk.np, P->prec, cand, 8);
@@ -792,7 +981,14 @@ qt_status me_plan_result(qt_me_plan *P, int32_t i, double *expect_out, double *r
     qt_stats sst;
     std::memset(&sst, 0, sizeof(sst));
     const void *ystate = nullptr;
-    if (!m.dense) {
+    if (m.res >= 0) {
+        const ResCtl &c = P->h_rctl[m.res];
+        status = c.status;
+        sst.n_accept = c.n_accept;
+        sst.n_reject = c.n_reject;
+        sst.n_rhs = c.n_rhs;
+        ystate = P->arena.at(m.o_vec);
+    } else if (!m.dense) {
         const CsrCtl &c = P->h_cctl[m.slot];
         status = c.status;
         parity = c.parity;
@@ -817,7 +1013,7 @@ qt_status me_plan_result(qt_me_plan *P, int32_t i, double *expect_out, double *r
     if (stats) *stats = sst;
     if (expect_out && m.ne > 0)
         QT_HIP(hipMemcpy(expect_out, P->arena.at(m.o_expect), (size_t)m.ne * m.nt * 16, hipMemcpyDeviceToHost));
-    if (rho_final && m.dense) {
+    if (rho_final && m.dense && m.res < 0) {
         const size_t np = (size_t)dense_np(m.d);
         std::vector<char> hv(np * np * es);
         QT_HIP(hipMemcpy(hv.data(), ystate, hv.size(), hipMemcpyDeviceToHost));
@@ -957,7 +1153,11 @@ qt_status qt_me_plan_time_rhs(qt_me_plan *P, int32_t reps, double *ms_per_launch
     QT_HIP(hipEventCreate(&e0));
     QT_HIP(hipEventCreate(&e1));
     QT_HIP(hipEventRecord(e0, s));
-    for (int32_t r = 0; r < reps; ++r) launch_dense_buckets(P, -1, s);
+    for (int32_t r = 0; r < reps; ++r) {  // a whole solve, as a run launches it
+        launch_dense_buckets(P, -1, s, false);
+        qt_status st = launch_resident(P, s);
+        if (st) return st;
+    }
     QT_HIP(hipEventRecord(e1, s));
     QT_HIP(hipGetLastError());
     QT_HIP(hipEventSynchronize(e1));
@@ -981,6 +1181,7 @@ qt_status qt_me_plan_destroy(qt_me_plan *P)
     for (hipStream_t ls : P->lane_streams) (void)hipStreamDestroy(ls);
     if (P->h_cctl) (void)hipHostFree(P->h_cctl);
     if (P->h_dctl) (void)hipHostFree(P->h_dctl);
+    if (P->h_rctl) (void)hipHostFree(P->h_rctl);
     P->arena.release();
     if (P->counted) P->ctx->refs--;
     delete P;

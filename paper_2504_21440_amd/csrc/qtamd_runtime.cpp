@@ -10,6 +10,7 @@
 #include "qt_csr.h"
 #include "qt_dense.h"
 #include "qt_host.h"
+#include "qt_res.h"
 
 namespace qt {
 
@@ -530,6 +531,8 @@ qt_status qt_liouvillian_build(qt_ctx *ctx, const qt_csr *H, int32_t n_c, const 
     L->d = d;
     L->nc = n_c;
     const size_t es = precision == QT_F64 ? sizeof(double2) : sizeof(float2);
+    L->res_w = res_width(A, cs, &L->res_band);
+    if (res_class(d, L->res_w, L->res_band, precision) < 0) L->res_w = 0;
 
     if (form == QT_FORM_DENSE) {
         const int32_t np = dense_np(d);
@@ -567,6 +570,7 @@ qt_status qt_liouvillian_build(qt_ctx *ctx, const qt_csr *H, int32_t n_c, const 
             delete L;
             return set_error(QT_EDEVICE, "upload dense operators");
         }
+        if (L->res_w) res_build_ell(A, cs, L->res_w, L->res_col, L->res_val);
         ctx->refs++, *out = L;
         return QT_OK;
     }

@@ -26,6 +26,7 @@
 #include "qt_csr.h"
 #include "qt_dense.h"
 #include "qt_host.h"
+#include "qt_res.h"
 #include "qt_tune.h"
 
 namespace qt {
@@ -82,6 +83,7 @@ struct Request {
     uint64_t ticket = 0;
     int32_t slot = -1;
     bool dense = false;
+    int32_t res = -1;  // kernel class of a resident request (kernels_res.hip), -1: not one
     int32_t d = 0, nt = 0, ne = 0, np = 0;
     size_t off = 0, bytes = 0;
     size_t o_expect = 0;  // offset inside the pool
@@ -107,7 +109,9 @@ struct qt_server {
     qt::CsrCtl *d_cctl = nullptr;
     qt::DenseInst *d_dinst = nullptr;
     qt::DenseCtl *d_dctl = nullptr;
-    int32_t *d_order = nullptr;
+    int32_t *d_order = nullptr;  // matrix-core problems by padded size, then resident ones by class
+    qt::ResInst *d_rinst = nullptr;
+    qt::ResCtl *d_rctl = nullptr;
     // The CSR part of an epoch (starting-step evaluations, then steps_per_epoch steps) is one graph
     // per lane, captured once per grid size: the live block count rounded up to a power of two, so
     // the workgroups past the live count that return at once never outnumber the live ones.  The
@@ -127,6 +131,7 @@ struct qt_server {
     Lane lanes[2];  // 0: large Liouvillians (context stream), 1: small ones (auxiliary stream)
     qt::CsrCtl *h_cctl = nullptr;   // pinned
     qt::DenseCtl *h_dctl = nullptr; // pinned
+    qt::ResCtl *h_rctl = nullptr;   // pinned
     std::vector<int32_t> free_slots;
     std::unordered_map<uint64_t, qt::Request> reqs;  // admitted or finished, not yet polled
     std::vector<uint64_t> active;                    // tickets resident on the device
@@ -255,7 +260,22 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
     const std::vector<int32_t> evidx = expect_vec_index(eptr, ecol, d, p->n_e);
     up(Ly.o_evidx, evidx.data(), evidx.size() * 4);
     qt_opts o = S->cfg.opts;
-    if (dense) {
+    const int rescls = res_problem(*p->L, dense, r.data()) ? res_class(d, p->L->res_w, p->L->res_band, S->prec) : -1;
+    ResInst ri;
+    std::vector<char> ell;  // alive until the uploads are waited for
+    if (rescls >= 0) {
+        res_fill_inst(&ri, *p->L, dense, p->n_t, p->n_e, base + Ly.o_rho0, base + Ly.o_vec,
+                      (const double *)(base + Ly.o_tlist), (const int32_t *)(base + Ly.o_eptr),
+                      (const int32_t *)(base + Ly.o_evidx), (const double2 *)(base + Ly.o_eval),
+                      (double2 *)(base + Ly.o_expect), o, 0.0);
+        ResCtl c;
+        std::memset(&c, 0, sizeof(c));
+        c.status = RES_ST_INIT;
+        S->h_rctl[slot] = c;
+        if (dense && res_upload_ell(*p->L, base + Ly.o_vec, ell, s) != QT_OK) e = hipErrorUnknown;
+        if (e == hipSuccess) e = hipMemcpyAsync(S->d_rinst + slot, &ri, sizeof(ri), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(S->d_rctl + slot, &S->h_rctl[slot], sizeof(c), hipMemcpyHostToDevice, s);
+    } else if (dense) {
         DenseInst g;
         dense_fill_inst(&g, d, p->L->nc, p->L->dense_creal, p->n_t, p->n_e, p->L->dense, base + Ly.o_rho0,
                         base + Ly.o_vec,
@@ -326,6 +346,7 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
     R.ticket = S->next_ticket++;
     R.slot = slot;
     R.dense = dense;
+    R.res = rescls;
     R.d = d;
     R.nt = p->n_t;
     R.ne = p->n_e;
@@ -419,7 +440,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     const int rpb = csr_rows_per_block(S->shape.lpr, S->shape.rg);
     for (uint64_t tk : S->active) {
         Request &R = S->reqs[tk];
-        if (R.dense) continue;
+        if (R.dense || R.res >= 0) continue;
         const int l = (int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0;
         for (int32_t b = 0; b < R.nblocks; ++b) {
             bi[l].push_back(R.slot);
@@ -431,10 +452,26 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     std::map<int32_t, std::vector<int32_t>> buckets;
     for (uint64_t tk : S->active) {
         Request &R = S->reqs[tk];
-        if (R.dense) buckets[-R.np].push_back(R.slot);  // largest first
+        if (R.dense && R.res < 0) buckets[-R.np].push_back(R.slot);  // largest first
     }
     std::vector<int32_t> order;
     for (auto &b : buckets) order.insert(order.end(), b.second.begin(), b.second.end());
+    // ---- resident requests: one launch per kernel class, largest problems first ----
+    std::vector<std::pair<int32_t, uint64_t>> rlist;
+    for (uint64_t tk : S->active)
+        if (S->reqs[tk].res >= 0) rlist.push_back({S->reqs[tk].res, tk});
+    std::stable_sort(rlist.begin(), rlist.end(), [&](const auto &a, const auto &b) {
+        return a.first != b.first ? a.first > b.first : S->reqs[a.second].d > S->reqs[b.second].d;
+    });
+    struct ResRun {
+        int32_t cls, start, count;
+    };
+    std::vector<ResRun> rruns;
+    for (auto &x : rlist) {
+        if (rruns.empty() || rruns.back().cls != x.first) rruns.push_back({x.first, (int32_t)order.size(), 0});
+        rruns.back().count++;
+        order.push_back(S->reqs[x.second].slot);
+    }
     hipEvent_t ev = nullptr;
     if (!order.empty()) {
         QT_HIP(hipMemcpyAsync(S->d_order, order.data(), order.size() * 4, hipMemcpyHostToDevice, s));
@@ -449,8 +486,10 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
                                 S->d_order + start, (int)b.second.size(), K, 0, bs);
             start += b.second.size();
         }
+        for (int b = bn; b < Ctx::NPOOL; ++b) QT_HIP(hipStreamWaitEvent(ctx->pool[b], ev, 0));
         QT_HIP(hipGetLastError());
     }
+    const bool mfma = !buckets.empty();
     // ---- large CSR lane (after the dense launches' start event, so those run beside it) ----
     hipEvent_t big_done = nullptr;
     if (!bi[0].empty()) {
@@ -462,24 +501,39 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
         QT_HIP(hipEventCreateWithFlags(&big_done, hipEventDisableTiming));
         QT_HIP(hipEventRecord(big_done, s));
     }
-    // ---- small CSR lane: replayed while the large lane runs and a small request still steps ----
-    if (!bi[1].empty()) {
+    // ---- small CSR lane and resident requests: replayed while the large lane runs and one of them still steps ----
+    if (!bi[1].empty() || !rruns.empty()) {
         hipStream_t sa = ctx->aux;
         constexpr int MAX_REPLAYS = 64;  // bounds an epoch, so that new requests are admitted
-        for (int rep = 0; rep < MAX_REPLAYS; ++rep) {
-            qt_status st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, sa);
-            if (st) {
-                if (big_done) (void)hipEventDestroy(big_done);
-                if (ev) (void)hipEventDestroy(ev);
-                return st;
+        qt_status st = QT_OK;
+        hipError_t e = hipSuccess;
+        for (int rep = 0; rep < MAX_REPLAYS && !st && e == hipSuccess; ++rep) {
+            for (size_t k = 0; k < rruns.size() && !st; ++k)
+                st = res_launch(rruns[k].cls, f64, S->d_rinst, S->d_rctl, S->d_order + rruns[k].start, rruns[k].count,
+                                K, 0, ctx->pool[(buckets.size() + k) % Ctx::NPOOL]);
+            if (!st && !bi[1].empty()) {
+                st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, sa);
+                if (!st)
+                    e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots,
+                                       hipMemcpyDeviceToHost, sa);
             }
-            QT_HIP(hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost,
-                                  sa));
-            QT_HIP(hipStreamSynchronize(sa));
+            if (!rruns.empty())
+                for (int b = 0; b < Ctx::NPOOL && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[b]);
+            if (!st && e == hipSuccess && !rruns.empty())
+                e = hipMemcpyAsync(S->h_rctl, S->d_rctl, sizeof(ResCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
+            if (e == hipSuccess) e = hipStreamSynchronize(sa);
             if (!big_done || hipEventQuery(big_done) != hipErrorNotReady) break;
             bool running = false;
             for (int32_t slot : csr_slots[1]) running = running || S->h_cctl[slot].status == ST_RUNNING;
+            for (auto &x : rlist) running = running || S->h_rctl[S->reqs[x.second].slot].status == ST_RUNNING;
             if (!running) break;
+        }
+        if (!st && e != hipSuccess)
+            st = set_error(QT_EDEVICE, std::string("qt_server_step: ") + hipGetErrorString(e));
+        if (st) {
+            if (big_done) (void)hipEventDestroy(big_done);
+            if (ev) (void)hipEventDestroy(ev);
+            return st;
         }
     }
     // ---- wait, then retire finished requests ----
@@ -489,7 +543,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     if (ev) {
         for (int b = 0; b < Ctx::NPOOL; ++b) QT_HIP(hipStreamSynchronize(ctx->pool[b]));
         (void)hipEventDestroy(ev);
-        QT_HIP(hipMemcpy(S->h_dctl, S->d_dctl, sizeof(DenseCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost));
+        if (mfma) QT_HIP(hipMemcpy(S->h_dctl, S->d_dctl, sizeof(DenseCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost));
     }
     int32_t fin = 0;
     std::vector<uint64_t> still;
@@ -498,7 +552,13 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
         int32_t status;
         qt_stats st;
         std::memset(&st, 0, sizeof(st));
-        if (R.dense) {
+        if (R.res >= 0) {
+            const ResCtl &c = S->h_rctl[R.slot];
+            status = c.status;
+            st.n_accept = c.n_accept;
+            st.n_reject = c.n_reject;
+            st.n_rhs = c.n_rhs;
+        } else if (R.dense) {
             const DenseCtl &c = S->h_dctl[R.slot];
             status = c.status;
             st.n_accept = c.n_accept;
@@ -568,7 +628,7 @@ static qt_status check_cfg(const qt_server_cfg *cfg)
 
 // Lays out the server's device memory in S->arena and returns the offsets through the members.
 struct ServerLayout {
-    size_t pool, cinst, cctl, dinst, dctl, order, ilist[2], counts[2], bi[2], br[2];
+    size_t pool, cinst, cctl, dinst, dctl, order, rinst, rctl, ilist[2], counts[2], bi[2], br[2];
 };
 static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap)
 {
@@ -580,6 +640,8 @@ static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap
     L.dinst = A.reserve(sizeof(DenseInst) * ns);
     L.dctl = A.reserve(sizeof(DenseCtl) * ns);
     L.order = A.reserve(sizeof(int32_t) * ns);
+    L.rinst = A.reserve(sizeof(ResInst) * ns);
+    L.rctl = A.reserve(sizeof(ResCtl) * ns);
     for (int k = 0; k < 2; ++k) {
         L.ilist[k] = A.reserve(sizeof(int32_t) * ns);
         L.counts[k] = A.reserve(sizeof(int32_t) * 2);
@@ -614,6 +676,8 @@ static qt_status server_create(Ctx *ctx, const qt_server_cfg *cfg, void *ws, siz
     S->d_dinst = (DenseInst *)A.at(Ly.dinst);
     S->d_dctl = (DenseCtl *)A.at(Ly.dctl);
     S->d_order = (int32_t *)A.at(Ly.order);
+    S->d_rinst = (ResInst *)A.at(Ly.rinst);
+    S->d_rctl = (ResCtl *)A.at(Ly.rctl);
     for (int k = 0; k < 2; ++k) {
         auto &ln = S->lanes[k];
         ln.d_ilist = (int32_t *)A.at(Ly.ilist[k]);
@@ -624,6 +688,7 @@ static qt_status server_create(Ctx *ctx, const qt_server_cfg *cfg, void *ws, siz
     }
     hipError_t e = hipHostMalloc((void **)&S->h_cctl, sizeof(CsrCtl) * ns, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void **)&S->h_dctl, sizeof(DenseCtl) * ns, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&S->h_rctl, sizeof(ResCtl) * ns, hipHostMallocDefault);
     if (e == hipSuccess) {
         // every slot starts finished: the kernels skip it until a request is admitted into it
         for (int i = 0; i < ns; ++i) {
@@ -631,10 +696,14 @@ static qt_status server_create(Ctx *ctx, const qt_server_cfg *cfg, void *ws, siz
             S->h_cctl[i].status = ST_DONE;
             std::memset(&S->h_dctl[i], 0, sizeof(DenseCtl));
             S->h_dctl[i].status = ST_DONE;
+            std::memset(&S->h_rctl[i], 0, sizeof(ResCtl));
+            S->h_rctl[i].status = ST_DONE;
         }
         e = hipMemcpyAsync(S->d_cctl, S->h_cctl, sizeof(CsrCtl) * ns, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(S->d_dctl, S->h_dctl, sizeof(DenseCtl) * ns, hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(S->d_rctl, S->h_rctl, sizeof(ResCtl) * ns, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     }
     if (e != hipSuccess) {
@@ -729,6 +798,7 @@ qt_status qt_server_destroy(qt_server *S)
     S->arena.release();
     if (S->h_cctl) (void)hipHostFree(S->h_cctl);
     if (S->h_dctl) (void)hipHostFree(S->h_dctl);
+    if (S->h_rctl) (void)hipHostFree(S->h_rctl);
     if (S->counted) S->ctx->refs--;
     delete S;
     return QT_OK;
