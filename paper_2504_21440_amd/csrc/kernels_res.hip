@@ -77,34 +77,6 @@ constexpr int res_elems(int dmax) { return (dmax + 2) * res_stride(dmax) + 3; }
 // reads need no offsets in registers and no address arithmetic.
 constexpr int RES_BAND = 6;
 
-// A uniform double in scalar registers.
-__device__ __forceinline__ double uni(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// The Runge-Kutta weights of a step, one per lane: a step forms h times all of them with one multiply,
-// and a use reads its lane into scalar registers.  (As literals they were hoisted out of the step loop
-// into some 60 vector registers.)
-enum { Q21, Q31, Q32, Q41, Q42, Q43, Q51, Q52, Q53, Q54, Q61, Q62, Q63, Q64, Q65, QB1, QB3, QB4, QB5, QB6,
-       QE1, QE3, QE4, QE5, QE6, QE7, QN };
-__device__ const double RES_Q[QN] = {
-    DP5::a21, DP5::a31, DP5::a32, DP5::a41, DP5::a42, DP5::a43, DP5::a51, DP5::a52, DP5::a53, DP5::a54,
-    DP5::a61, DP5::a62, DP5::a63, DP5::a64, DP5::a65, DP5::b1, DP5::b3, DP5::b4, DP5::b5, DP5::b6,
-    DP5::e1, DP5::e3, DP5::e4, DP5::e5, DP5::e6, DP5::e7};
-__device__ __forceinline__ double lane_of(double v, int l)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ float lane_of(float v, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
 template <typename T, int TPB, int R, int W>
 __global__ __launch_bounds__(TPB) void k_res(const ResInst *__restrict__ insts, ResCtl *__restrict__ ctls,
                                              const int32_t *__restrict__ order, int budget, int reset)
@@ -233,9 +205,9 @@ __global__ __launch_bounds__(TPB) void k_res(const ResInst *__restrict__ insts, 
     auto fence = [] {
         if constexpr (R * sizeof(T) >= 20) __builtin_amdgcn_sched_barrier(0);
     };
-    // (L x) of every own element for the x in matrix B, two accumulation chains per component.  The
-    // offsets are unpacked at every use (an opaque copy): unpacked once, they would take the
-    // registers that the elements need.
+    // (L x) of every own element for the x in matrix B, two accumulation chains per component.  With
+    // several elements a thread, packed offsets are unpacked at every use (an opaque copy): unpacked
+    // once, they would take the registers that the elements need.
     auto apply = [&](auto B, V(&out)[R]) {
         const char *x = smem + decltype(B)::value * LB;
 #pragma unroll
@@ -257,7 +229,7 @@ __global__ __launch_bounds__(TPB) void k_res(const ResInst *__restrict__ insts, 
 #pragma unroll
                 for (int k = 0; k < W; k += 2) {
                     uint32_t o = off[m][k >> 1];
-                    asm volatile("" : "+v"(o));
+                    if constexpr (R > 1) asm volatile("" : "+v"(o));
                     const V z = *(const V *)(x + (o & 0xffffu));
                     pr = fma(val[m][k].x, z.x, pr);
                     nr = fma(val[m][k].y, z.y, nr);
@@ -320,7 +292,7 @@ __global__ __launch_bounds__(TPB) void k_res(const ResInst *__restrict__ insts, 
     };
 
     V y[R], k1[R], lk[R];
-    const double ql = RES_Q[min(lane, (int)QN - 1)];
+    const double ql = DP5_Q[min(lane, (int)QN - 1)];
     double t, h, lprev, err_prev, tr0;
     int status, save_idx, last_rejected;
     int64_t n_accept, n_reject, n_steps, n_rhs;

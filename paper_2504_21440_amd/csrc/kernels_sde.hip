@@ -47,7 +47,7 @@ __global__ __launch_bounds__(SDE_THREADS) __attribute__((amdgpu_waves_per_eu(OCC
 {
     using V = typename vec2<T>::type;
     const SdeParams &P = *Pp;
-    extern __shared__ char smem[];
+    extern __shared__ __align__(16) char smem[];  // 16-byte LDS accesses: off by 8 bytes they take hundreds of cycles
     const int n = P.n, m = P.m;
     V *xs = (V *)smem;  // the vector the gathers read
     V *bx = xs + n;     // B_k x at the thread's own rows, m blocks of n

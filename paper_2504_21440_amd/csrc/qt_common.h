@@ -127,6 +127,35 @@ struct DP5 {
     static constexpr double e7 = -1.0 / 40.0;
 };
 
+// A value every lane holds alike, in scalar registers: what is computed from it is uniform for the
+// compiler too (scalar branches and counters instead of vector registers and masks).
+__device__ __forceinline__ double uni(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The Runge-Kutta weights of a step, one per lane: a step forms h times all of them with one multiply,
+// and a use reads its lane into scalar registers.  (As literals they were hoisted out of the step loop
+// into some 60 vector registers.)
+enum { Q21, Q31, Q32, Q41, Q42, Q43, Q51, Q52, Q53, Q54, Q61, Q62, Q63, Q64, Q65, QB1, QB3, QB4, QB5, QB6,
+       QE1, QE3, QE4, QE5, QE6, QE7, QN };
+__device__ constexpr double DP5_Q[QN] = {
+    DP5::a21, DP5::a31, DP5::a32, DP5::a41, DP5::a42, DP5::a43, DP5::a51, DP5::a52, DP5::a53, DP5::a54,
+    DP5::a61, DP5::a62, DP5::a63, DP5::a64, DP5::a65, DP5::b1, DP5::b3, DP5::b4, DP5::b5, DP5::b6,
+    DP5::e1, DP5::e3, DP5::e4, DP5::e5, DP5::e6, DP5::e7};
+__device__ __forceinline__ double lane_of(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float lane_of(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
 // ---- step-size control (FP64) ----
 // accepted step: h_new = h * clamp(0.9 err^-0.17 err_prev^0.04, 0.2, 10)
 __device__ __forceinline__ double pi_factor(double err, double err_prev)

@@ -6,6 +6,7 @@
 // proportional to |C_k psi|^2, then psi <- C_k psi / |C_k psi| and a new threshold is drawn.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace qt {
@@ -51,6 +52,9 @@ struct McParams {
     const int32_t *cweight;   // [nc]: coefficient (index into coefs) of collapse channel k, -1 for constant
 };
 
+// The kernel that holds A in registers for this problem (kernels_mc_reg.hip), its workgroup size and LDS
+// bytes; null when the problem has none.
+const void *mc_reg_kernel(const McParams &p, bool f64, bool td, int *threads, size_t *lds);
 // td: the plan has time-dependent terms (the weighted kernel)
 void mc_launch(const McParams &p, const McParams *dev_p, bool f64, bool td, int grid, hipStream_t s);
 int mc_grid(const McParams &p, bool f64, bool td, int device);
