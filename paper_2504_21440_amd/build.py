@@ -16,12 +16,13 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqtamd.so")
 SOURCES = ["kernels_csr.hip", "kernels_csr_td.hip", "kernels_assembly.hip", "kernels_dense.hip", "kernels_res.hip", "kernels_mc.hip", "kernels_mc_reg.hip",
-           "kernels_sde.hip", "qtamd_sde.cpp", "qtamd_noalloc.hip", "kernels_util.hip",
+           "kernels_sde.hip", "kernels_sde_reg.hip", "qtamd_sde.cpp", "qtamd_noalloc.hip", "kernels_util.hip",
            "qtamd_runtime.cpp", "qtamd_me.cpp", "qtamd_mc.cpp", "qtamd_server.cpp", "qtamd_tune.cpp"]
 ARCH = "gfx950"
 # kernels_res.hip: the step loop fills the register file; hoisting the FP64 constants of its logarithm and
 # exponential out of the loop took 45 registers per lane (127 against 82 for one element per thread).
-EXTRA = {k: ["-mllvm", "-disable-machine-licm"] for k in ("kernels_res.hip", "kernels_mc.hip", "kernels_mc_reg.hip")}
+EXTRA = {k: ["-mllvm", "-disable-machine-licm"] for k in ("kernels_res.hip", "kernels_mc.hip", "kernels_mc_reg.hip",
+                                                           "kernels_sde_reg.hip")}
 
 
 def _hipcc():

@@ -335,19 +335,25 @@ static const void *sde_kernel(const SdeParams &p, bool f64)
 int sde_grid(const SdeParams &p, bool f64, int device)
 {
     const void *fn = sde_kernel(p, f64);
-    const size_t lds = sde_lds_bytes(p, f64);
+    size_t lds = sde_lds_bytes(p, f64);
+    int threads = SDE_THREADS;
+    if (const void *reg = sde_reg_kernel(p, f64, &threads)) fn = reg, lds = 0;
     if (lds > 65536) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, SDE_THREADS, lds) != hipSuccess || per_cu < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess || per_cu < 1)
         per_cu = 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>(p.ntraj, (int64_t)per_cu * device_cus(device)));
 }
 
 void sde_launch(const SdeParams &p, const SdeParams *dev_p, bool f64, int grid, hipStream_t s)
 {
-    const void *fn = sde_kernel(p, f64);
     void *args[] = {(void *)&dev_p};
-    (void)hipLaunchKernel(fn, dim3(grid), dim3(SDE_THREADS), args, sde_lds_bytes(p, f64), s);
+    int threads = SDE_THREADS;
+    if (const void *reg = sde_reg_kernel(p, f64, &threads)) {
+        (void)hipLaunchKernel(reg, dim3(grid), dim3(threads), args, 0, s);
+        return;
+    }
+    (void)hipLaunchKernel(sde_kernel(p, f64), dim3(grid), dim3(SDE_THREADS), args, sde_lds_bytes(p, f64), s);
 }
 
 }  // namespace qt

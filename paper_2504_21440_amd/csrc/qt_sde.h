@@ -42,6 +42,9 @@ struct SdeParams {
     unsigned long long *queue;
 };
 
+// The kernel that holds the operators in registers for this problem (kernels_sde_reg.hip) and its workgroup
+// size; null when the problem has none.
+const void *sde_reg_kernel(const SdeParams &p, bool f64, int *threads);
 size_t sde_lds_bytes(const SdeParams &p, bool f64);
 // Sets p.occ2 from the ensemble size and the device's compute-unit count.
 void sde_choose_variant(SdeParams &p, bool f64, int device);
