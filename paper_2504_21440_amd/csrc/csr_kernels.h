@@ -711,19 +711,18 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_stage(const CsrInst *__rest
 // double-buffered: this launch reads rd and writes wr, stages 3..7 read wr, and the next step's
 // launch swaps them.  rd->pending is 0 right after the starting step (no stage 7 to decide yet).
 // Removes the control launch from every step.
-template <typename T, int LPR, int RG, bool TD>
-__global__ __launch_bounds__(CSR_THREADS) void k_csr_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
-                                                                CsrCtl *__restrict__ wr)
+//
+// ctl_fold: the decision, into nsh (shared) and, from workgroup 0, into wr; false for a finished problem.
+// cw2 (shared, time-dependent problems): stage 2's coefficient row when a step was decided.
+template <typename V, bool TD>
+__device__ __forceinline__ bool ctl_fold(const CsrInst &I, const CsrCtl *__restrict__ rd, CsrCtl *__restrict__ wr,
+                                         CsrCtl &nsh, V *cw2)
 {
-    using V = typename vec2<T>::type;
-    const CsrInst &I = one;
     __shared__ double scr[32];
-    __shared__ CsrCtl nsh;
-    __shared__ V cw2[TD ? TD_MAX_TERMS + 1 : 1];
     const CsrCtl c = *rd;
     if (c.status != ST_RUNNING || c.phase != PH_STEP) {  // finished: carry the record forward
         if (blockIdx.x == 0 && threadIdx.x == 0) *wr = c;
-        return;
+        return false;
     }
     if (c.pending) {
         const int sidx = c.save_idx;
@@ -744,7 +743,6 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_stage2_ctl(const CsrInst on
     if (threadIdx.x == 0) nsh.pending = 1;
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) *wr = nsh;
-    const V *cw = nullptr;  // stage 2's coefficient row (time-dependent problems)
     if constexpr (TD) {
         if (c.pending && nsh.status == ST_RUNNING && I.nterms > 0) {
             // the rows of the new step's evaluations, as the control kernel forms them
@@ -755,10 +753,23 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_stage2_ctl(const CsrInst on
                 cw2[threadIdx.x] = from_d2<V>(w2);
             }
             __syncthreads();
-            cw = cw2;
         }
     }
-    stage_body<T, LPR, RG, 2, true, true, TD>(I, &nsh, blockIdx.x * CsrGeom<LPR, RG>::RPB, blockIdx.x, cw);
+    return true;
+}
+
+template <typename T, int LPR, int RG, bool TD>
+__global__ __launch_bounds__(CSR_THREADS) void k_csr_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
+                                                                CsrCtl *__restrict__ wr)
+{
+    using V = typename vec2<T>::type;
+    __shared__ CsrCtl nsh;
+    __shared__ V cw2[TD ? TD_MAX_TERMS + 1 : 1];
+    if (!ctl_fold<V, TD>(one, rd, wr, nsh, cw2)) return;
+    const V *cw = nullptr;  // stage 2's coefficient row (time-dependent problems)
+    if constexpr (TD)
+        if (rd->pending && nsh.status == ST_RUNNING && one.nterms > 0) cw = cw2;
+    stage_body<T, LPR, RG, 2, true, true, TD>(one, &nsh, blockIdx.x * CsrGeom<LPR, RG>::RPB, blockIdx.x, cw);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -880,6 +891,9 @@ template <bool TD> static bool launch_stage2_ctl(const CsrLaunch &L, const CsrAr
 
 // Defined in kernels_csr_td.hip: the time-dependent SpMV kernels first..last.
 void csr_td_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last);
+// Defined in kernels_op.hip: the operator-form kernels first..last, and stage 2 with the folded control.
+void op_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last);
+void op_stage2_ctl(const CsrLaunch &L, const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr);
 // Defined in kernels_csr_td.hip: launch_stage2_ctl<true>.
 bool csr_td_stage2_ctl(const CsrLaunch &L, const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr);
 

@@ -337,7 +337,8 @@ static void launch_control(const CsrArgs &a, int step_mode)
 
 static void spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last)
 {
-    if (L.td) csr_td_spmv(L, a, first, last);
+    if (L.op) op_spmv(L, a, first, last);
+    else if (L.td) csr_td_spmv(L, a, first, last);
     else launch_spmv_range<false>(L, a, first, last);
 }
 
@@ -366,7 +367,8 @@ void csr_launch_step(const CsrLaunch &L, hipStream_t s, int j)
     if (L.fused && j >= 0 && a.use_one) {
         // step j reads record j % 2 and writes the other (see k_csr_stage2_ctl)
         CsrCtl *rd = L.ctls + (j & 1), *wr = L.ctls + ((j + 1) & 1);
-        const bool launched = L.td ? csr_td_stage2_ctl(L, a, rd, wr) : launch_stage2_ctl<false>(L, a, rd, wr);
+        if (L.op) op_stage2_ctl(L, a, rd, wr);
+        const bool launched = L.op ? true : L.td ? csr_td_stage2_ctl(L, a, rd, wr) : launch_stage2_ctl<false>(L, a, rd, wr);
         if (launched) {
             a.ctls = wr;
             spmv(L, a, 3, 7);

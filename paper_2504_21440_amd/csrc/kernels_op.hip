@@ -1,0 +1,469 @@
+// kernels_op.hip -- the staged solver's right-hand side in operator form on gfx950.
+//
+// The superoperator of a chain of L spins has 4^L (1 + 2 L + L / 4) entries: 12 or 20 bytes of matrix per
+// complex multiply-add, streamed at every stage (317 / 531 MB at L = 10), although it is made of d x d
+// operators.  Where A = -i H - 1/2 sum C^dag C has few off-diagonal entries per row and every collapse
+// operator at most one entry per row, the kernels here apply
+//     L(rho)_ij = (A_ii + conj A_jj) rho_ij + sum_k A_ik rho_kj + sum_l conj(A_jl) rho_il
+//               + sum_c C_c(i, k_c(i)) conj(C_c(j, k_c(j))) rho_{k_c(i) k_c(j)}
+// from tables of a few hundred KB that stay in the caches, so the only memory traffic left is the state
+// vectors.  The state is exactly Hermitian (the caller checks the initial one), so only the tiles on and
+// above the diagonal are evaluated, and a workgroup writes its elements and, transposed through LDS, their
+// conjugates below: half the sums and half the reads of the epilogue.
+//
+// What bounds it: one chain of L = 8 (complex64, 160 workgroups) the latency of a wave, kernel by kernel --
+// 5.0 us a stage, of which the launch is about 2 -- so there a wave takes one row and requests every source
+// before the first sum; with two rows it took 6.1 us, with the sources requested as they are used 5.3 us.
+// L = 10 (complex128) the vector L1: 30 sources and 20 table words per element at 4 lanes a cycle are 12 us,
+// beside 130 MB of state vectors from the L2s and the MALL; 28 us a stage (118 us for the matrix kernels, which
+// stream 531 MB; 40 us without the Hermitian halving).  Two rows a wave read each column entry for two
+// elements; four rows took 40 us (too few waves in flight), one row 33 us.  Sixteen chains of L = 8: 19 us a
+// stage against 45 to 60 us.
+//
+// The diagonal is formed in FP64 and rounded once, as the assembled matrix holds it.  Everything else of a
+// step -- stage combinations, error partials, control, expectation values -- is that of kernels_csr.hip, on
+// the same descriptors, with op_blocks(d) partials a problem.
+#include <type_traits>
+
+#include "csr_kernels.h"
+
+namespace qt {
+
+// Scalar (uniform) views of a row's record: the constant address space makes the compiler read it with
+// scalar loads, which the stores of the epilogue would otherwise rule out.
+#define QT_CONST __attribute__((address_space(4)))
+typedef float uf2 __attribute__((ext_vector_type(2)));
+typedef double ud2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float2 uld(const float2 *p)
+{
+    const uf2 v = *(const QT_CONST uf2 *)p;
+    return make_float2(v.x, v.y);
+}
+__device__ __forceinline__ double2 uld(const double2 *p)
+{
+    const ud2 v = *(const QT_CONST ud2 *)p;
+    return make_double2(v.x, v.y);
+}
+__device__ __forceinline__ int32_t uld(const int32_t *p) { return *(const QT_CONST int32_t *)p; }
+
+// The element at a 32-bit byte offset of a vector (one address register, the base in scalar ones; vectors
+// hold up to 4 GB: d <= OP_MAX_D).
+template <typename V> __device__ __forceinline__ V at(const V *p, uint32_t off)
+{
+    return gld((const V *)((const char *)p + off));
+}
+template <typename P> __device__ __forceinline__ P *uniform_ptr(P *p)
+{
+    const uint64_t b = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return (P *)(((uint64_t)hi << 32) | lo);
+}
+
+// Rows and columns of a workgroup and of this wave: four waves' rows, RB each, of a 64 x 64 tile on or above
+// the diagonal.  Row b of the triangle of T tiles has T - b of them; rows b and T - 1 - b together have
+// T + 1, which makes the tile of a number one division.
+template <int RB> struct OpItem {
+    static constexpr int ROWS = 4 * RB;
+    int ib, jb;  // the workgroup's first row and column
+    int i0, j;   // this wave's first row; this lane's column (past the end: the last)
+    bool jok;
+    int i[RB];   // rows (past the end: the last)
+    __device__ __forceinline__ OpItem(int blk, int d)
+    {
+        const int T = (d + 63) / 64, q = blk / (64 / ROWS), sub = blk % (64 / ROWS);
+        int b = q / (T + 1), t = q % (T + 1);
+        if (t < T - b) {
+            t += b;
+        } else {
+            t -= T - b;
+            b = T - 1 - b;
+            t += b;
+        }
+        ib = b * 64 + sub * ROWS;
+        jb = t * 64;
+        i0 = ib + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * RB;
+        const int jl = jb + (int)(threadIdx.x & 63);
+        jok = jl < d;
+        j = jok ? jl : d - 1;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) i[r] = min(i0 + r, d - 1);
+    }
+    // whether this lane holds an element of the upper triangle in its row r
+    __device__ __forceinline__ bool has(int r, int d) const { return jok && i0 + r < d && i0 + r <= j; }
+};
+
+// The elements below the diagonal, conj of those above: a workgroup's rows x 64 columns through LDS, so that
+// runs of ROWS elements are written.  Uniform over the workgroup.
+template <typename V, int RB> struct OpMirror {
+    static constexpr int ROWS = 4 * RB;
+    V m[ROWS][65];  // 65: the columns of a row and the rows of a column both start in different banks
+};
+template <typename V, int RB>
+__device__ __forceinline__ void op_mirror(const OpMirror<V, RB> &sh, const OpItem<RB> &it, int d, V *out)
+{
+    constexpr int ROWS = 4 * RB;
+#pragma unroll
+    for (int n = 0; n < RB; ++n) {
+        const int e = n * CSR_THREADS + (int)threadIdx.x, r = e % ROWS, c = e / ROWS;
+        const int i = it.ib + r, j = it.jb + c;
+        if (j < d && i < j) {  // i < j: also i < d
+            V v = sh.m[r][c];
+            v.y = -v.y;
+            gst((V *)((char *)out + (uint32_t)(j * d + i) * (uint32_t)sizeof(V)), v);
+        }
+    }
+}
+
+// L x at the wave's RB rows in this lane's column; x(o) is the input at byte offset o.  The loops run over
+// the entries, four at a time for all rows: 4 RB sources are in flight at once, a column's entries are read
+// once for the RB rows, and nothing but the sums stays in registers.
+template <typename T, int RB, typename X>
+__device__ __forceinline__ void op_sum(const OpForm &O, int d, const OpItem<RB> &it, X x,
+                                       typename vec2<T>::type (&acc)[RB])
+{
+    using V = typename vec2<T>::type;
+    constexpr uint32_t ES = sizeof(V);
+    const int w = O.w;
+    const uint32_t ds = (uint32_t)d * ES, jo = (uint32_t)it.j * ES;
+    const V *__restrict__ aval = uniform_ptr((const V *)O.aval);
+    const V *__restrict__ cval = uniform_ptr((const V *)O.cval);
+    const int32_t *__restrict__ lcol = uniform_ptr(O.lcol);
+    const int32_t *rac[RB];
+    const V *rav[RB];
+    const double2 dj = gld(O.diag + it.j);
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const char *rec = uniform_ptr((const char *)O.rows) + (size_t)it.i[r] * ((size_t)w * (8 + 2 * ES));
+        rac[r] = (const int32_t *)rec;              // [w] columns of A, [w] columns of the jumps
+        rav[r] = (const V *)(rec + 8 * (size_t)w);  // [w] values of A, [w] of the jumps
+        const double2 di = uld(O.diag + it.i[r]);
+        V dd;
+        dd.x = (T)(di.x + dj.x);
+        dd.y = (T)(di.y - dj.y);
+        acc[r].x = acc[r].y = T(0);
+        cfma(acc[r], dd, x((uint32_t)it.i[r] * ds + jo));
+    }
+    // M entries at a time for all rows.  One row (small problems, bound by the latency of a wave): every source
+    // is requested before the first sum; more: up to M RB sources in flight.
+    auto part = [&](auto count, int k) {
+        constexpr int M = decltype(count)::value;
+        V a[M], c[M], up[RB][M], side[RB][M], jump[RB][M];
+        uint32_t l[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const uint32_t q = (uint32_t)((k + m) * d + it.j);
+            l[m] = (uint32_t)gld(lcol + q);
+            a[m] = at(aval, q * ES);
+            a[m].y = -a[m].y;
+            c[m] = at(cval, q * ES);
+        }
+        // A rho: the column's other rows
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int m = 0; m < M; ++m) up[r][m] = x((uint32_t)uld(rac[r] + k + m) * ds + jo);
+        auto load_side = [&]() {  // rho A^dag: the row's other columns
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (l[m] & 0xffffu) * ES);
+        };
+        auto load_jump = [&]() {  // the jumps; an element without one takes itself, times zero
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int ki = uld(rac[r] + w + k + m);
+                    const bool has = ki >= 0 && (l[m] >> 16) != 0xffffu;
+                    jump[r][m] = x(has ? (uint32_t)ki * ds + (l[m] >> 16) * ES : (uint32_t)it.i[r] * ds + jo);
+                }
+        };
+        if constexpr (RB == 1) {
+            load_side();
+            load_jump();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int m = 0; m < M; ++m) cfma(acc[r], uld(rav[r] + k + m), up[r][m]);
+        if constexpr (RB > 1) load_side();
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int m = 0; m < M; ++m) cfma(acc[r], a[m], side[r][m]);
+        if constexpr (RB > 1) load_jump();
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int m = 0; m < M; ++m) cfma(acc[r], cmulc(uld(rav[r] + w + k + m), c[m]), jump[r][m]);
+    };
+    int k = 0;
+    if constexpr (RB == 1) {
+#pragma unroll 1
+        for (; k + 8 <= w; k += 8) part(std::integral_constant<int, 8>{}, k);
+    }
+#pragma unroll 1
+    for (; k + 4 <= w; k += 4) part(std::integral_constant<int, 4>{}, k);
+    if (k < w) part(std::integral_constant<int, 2>{}, k);
+}
+
+// Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.
+template <typename T, int RB>
+__device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, int blk, int which)
+{
+    using V = typename vec2<T>::type;
+    __shared__ double scr[16];
+    __shared__ OpMirror<V, RB> tr;
+    if (C->status != ST_RUNNING || C->phase != (which ? PH_INIT1 : PH_INIT0)) return;
+    const int d = I.d;
+    const OpItem<RB> it(blk, d);
+    const double h0 = C->h0;
+    const T th0 = (T)h0;
+    const V *__restrict__ x0 = uniform_ptr((const V *)I.rho0);
+    V *__restrict__ y = uniform_ptr((V *)I.Y[0]);
+    V *__restrict__ k1 = uniform_ptr((V *)I.K[0]);
+    double sa = 0.0, sb = 0.0;
+    if (it.i0 < d) {
+        V acc[RB];
+        if (which)
+            op_sum<T, RB>(I.op, d, it, [&](uint32_t o) {
+                V v = at((const V *)y, o);
+                caxpy(v, th0, at((const V *)k1, o));
+                return v;
+            }, acc);
+        else
+            op_sum<T, RB>(I.op, d, it, [&](uint32_t o) { return at(x0, o); }, acc);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            if (!it.has(r, d)) continue;
+            const uint32_t row = (uint32_t)(it.i[r] * d + it.j) * (uint32_t)sizeof(V);
+            const double wt = it.j > it.i[r] ? 2.0 : 1.0;  // the element below the diagonal counts as well
+            if (which) {
+                const double2 yr = to_d2(at((const V *)y, row)), f0 = to_d2(at((const V *)k1, row)), f1 = to_d2(acc[r]);
+                const double sc = I.atol + I.rtol * sqrt(yr.x * yr.x + yr.y * yr.y);
+                const double dx = (f1.x - f0.x) / h0, dy = (f1.y - f0.y) / h0;
+                sa += wt * ((dx * dx + dy * dy) / (sc * sc));
+            } else {
+                const V yv = at(x0, row);
+                gst((V *)((char *)k1 + row), acc[r]);
+                gst((V *)((char *)y + row), yv);
+                tr.m[it.i0 - it.ib + r][threadIdx.x & 63] = acc[r];
+                const double sc = I.atol + I.rtol * sqrt(abs2d(yv));
+                sa += wt * (abs2d(yv) / (sc * sc));
+                sb += wt * (abs2d(acc[r]) / (sc * sc));
+            }
+        }
+    }
+    if (!which) {
+        __syncthreads();
+        op_mirror(tr, it, d, k1);
+        // the initial state is copied below the diagonal as well
+#pragma unroll
+        for (int n = 0; n < RB; ++n) {
+            const int e = n * CSR_THREADS + (int)threadIdx.x, i = it.ib + e % (4 * RB), j = it.jb + e / (4 * RB);
+            const uint32_t o = (uint32_t)(j * d + i) * (uint32_t)sizeof(V);
+            if (j < d && i < j) gst((V *)((char *)y + o), at(x0, o));
+        }
+    }
+    sa = block_sum(sa, scr);
+    if (!which) sb = block_sum(sb, scr);
+    if (threadIdx.x == 0) {
+        I.partials[2 * blk] = sa;
+        if (!which) I.partials[2 * blk + 1] = sb;
+    }
+}
+
+// One Runge-Kutta stage S (2..7), uniform over the launch.
+template <typename T, int RB>
+__device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C, int blk, int S)
+{
+    using V = typename vec2<T>::type;
+    __shared__ double scr[16];
+    __shared__ OpMirror<V, RB> tk, tx;
+    const int d = I.d;
+    const OpItem<RB> it(blk, d);
+    if (C->status != ST_RUNNING || C->phase != PH_STEP) return;
+    const double h = C->h_try;
+    const int p = C->parity;
+    const T s = (T)C->scale;
+    const V *__restrict__ y = uniform_ptr((const V *)I.Y[p]);
+    const V *__restrict__ k1 = uniform_ptr((const V *)I.K[p]);
+    const V *__restrict__ ynew = uniform_ptr((const V *)I.Y[1 - p]);
+    const V *__restrict__ xin = uniform_ptr(S == 2 ? k1 : (const V *)(S == 7 ? I.Y[1 - p] : I.ys[S & 1 ? 0 : 1]));
+    // where the stage's derivative and the next stage's input go
+    V *__restrict__ kout = uniform_ptr((V *)(S == 7 ? I.K[1 - p] : I.ks[S == 7 ? 0 : S - 2]));
+    V *__restrict__ xout = uniform_ptr((V *)(S == 6 ? I.Y[1 - p] : I.ys[S & 1]));
+    const V *__restrict__ q0 = uniform_ptr((const V *)(S == 7 ? I.ks[4] : I.ks[0]));
+    const V *__restrict__ q1 = uniform_ptr((const V *)I.ks[1]);
+    const V *__restrict__ q2 = uniform_ptr((const V *)I.ks[2]);
+    const V *__restrict__ q3 = uniform_ptr((const V *)I.ks[3]);
+    double e2 = 0.0, l2 = 0.0;
+    if (it.i0 < d) {
+        V acc[RB], yr, k1r, kr[4]{}, ynr{};
+        auto operands = [&](int r) {  // of the stage combination
+            const uint32_t row = (uint32_t)(it.i[r] * d + it.j) * (uint32_t)sizeof(V);
+            yr = at(y, row);
+            k1r = at(k1, row);
+            if ((S >= 3 && S <= 5) || S == 7) kr[0] = at(q0, row);
+            if (S >= 4) kr[1] = at(q1, row);
+            if (S >= 5) kr[2] = at(q2, row);
+            if (S >= 6) kr[3] = at(q3, row);
+            if (S == 7) ynr = at(ynew, row);
+        };
+        if constexpr (RB == 1) operands(0);
+        op_sum<T, RB>(I.op, d, it, [&](uint32_t o) { return at(xin, o); }, acc);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            if (!it.has(r, d)) continue;
+            const uint32_t row = (uint32_t)(it.i[r] * d + it.j) * (uint32_t)sizeof(V);
+            if constexpr (RB > 1) operands(r);
+            V a = acc[r];
+            yr = cscale(yr, s);
+            k1r = cscale(k1r, s);
+            V o = yr;
+            if (S == 2) {
+                // k2 = L (y + a21 h k1) = k1 + a21 h (L k1); the trace scale applies to y and k1 alike
+                const V lk1 = a;
+                a = k1r;
+                caxpy(a, (T)(h * DP5::a21) * s, lk1);
+                caxpy(o, (T)(h * DP5::a31), k1r);
+                caxpy(o, (T)(h * DP5::a32), a);
+            } else if (S == 3) {
+                caxpy(o, (T)(h * DP5::a41), k1r);
+                caxpy(o, (T)(h * DP5::a42), kr[0]);
+                caxpy(o, (T)(h * DP5::a43), a);
+            } else if (S == 4) {
+                caxpy(o, (T)(h * DP5::a51), k1r);
+                caxpy(o, (T)(h * DP5::a52), kr[0]);
+                caxpy(o, (T)(h * DP5::a53), kr[1]);
+                caxpy(o, (T)(h * DP5::a54), a);
+            } else if (S == 5) {
+                caxpy(o, (T)(h * DP5::a61), k1r);
+                caxpy(o, (T)(h * DP5::a62), kr[0]);
+                caxpy(o, (T)(h * DP5::a63), kr[1]);
+                caxpy(o, (T)(h * DP5::a64), kr[2]);
+                caxpy(o, (T)(h * DP5::a65), a);
+            } else if (S == 6) {
+                caxpy(o, (T)(h * DP5::b1), k1r);
+                caxpy(o, (T)(h * DP5::b3), kr[1]);
+                caxpy(o, (T)(h * DP5::b4), kr[2]);
+                caxpy(o, (T)(h * DP5::b5), kr[3]);
+                caxpy(o, (T)(h * DP5::b6), a);
+            } else {
+                double2 e = make_double2(0.0, 0.0);
+                caxpy(e, h * DP5::e1, to_d2(k1r));
+                caxpy(e, h * DP5::e3, to_d2(kr[1]));
+                caxpy(e, h * DP5::e4, to_d2(kr[2]));
+                caxpy(e, h * DP5::e5, to_d2(kr[3]));
+                caxpy(e, h * DP5::e6, to_d2(kr[0]));
+                caxpy(e, h * DP5::e7, to_d2(a));
+                const double sc = I.atol + I.rtol * sqrt(fmax(abs2d(yr), abs2d(ynr)));
+                const double wt = it.j > it.i[r] ? 2.0 : 1.0;  // the element below the diagonal counts as well
+                e2 += wt * ((e.x * e.x + e.y * e.y) / (sc * sc));
+                l2 += wt * abs2d(a);
+            }
+            gst((V *)((char *)kout + row), a);
+            tk.m[it.i0 - it.ib + r][threadIdx.x & 63] = a;
+            if (S < 7) {
+                gst((V *)((char *)xout + row), o);
+                tx.m[it.i0 - it.ib + r][threadIdx.x & 63] = o;
+            }
+        }
+    }
+    __syncthreads();
+    op_mirror(tk, it, d, kout);
+    if (S < 7) op_mirror(tx, it, d, xout);
+    if (S == 7) {
+        e2 = block_sum(e2, scr);
+        const bool steady = I.steady_tol2 > 0.0;
+        if (steady) l2 = block_sum(l2, scr);
+        if (threadIdx.x == 0) {
+            I.partials[2 * blk] = e2;
+            if (steady) I.partials[2 * blk + 1] = l2;
+        }
+    }
+}
+
+// what: 0 / 1 the starting-step evaluations, 2..7 a stage.  ONE: one problem, descriptor by value, blocks in
+// XCD-contiguous order (a row's sources are then mostly rows of the same XCD's L2); otherwise the block
+// table (bi: problem, br: its block).
+template <typename T, int RB, bool ONE, bool INIT>
+__global__ __launch_bounds__(CSR_THREADS) void k_op(const CsrInst *__restrict__ insts, const CsrInst one,
+                                                    const CsrCtl *__restrict__ ctls, const int32_t *__restrict__ bi,
+                                                    const int32_t *__restrict__ br, int xcd,
+                                                    const int32_t *__restrict__ bound, int what)
+{
+    const int lb = csr_block(xcd);
+    if constexpr (ONE) {
+        if constexpr (INIT) op_init_body<T, RB>(one, ctls, lb, what);
+        else op_stage_body<T, RB>(one, ctls, lb, what);
+    } else {
+        if (bound && lb >= bound[0]) return;
+        const int ii = bi[lb], blk = br[lb];
+        const CsrInst &I = insts[ii];
+        // one launch serves both row counts: the dimension decides
+        if (I.d > OP_SMALL_D) {
+            if constexpr (INIT) op_init_body<T, OP_ROWS>(I, ctls + ii, blk, what);
+            else op_stage_body<T, OP_ROWS>(I, ctls + ii, blk, what);
+        } else {
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL>(I, ctls + ii, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL>(I, ctls + ii, blk, what);
+        }
+    }
+}
+
+// Stage 2 with the previous step's control folded in, as k_csr_stage2_ctl.
+template <typename T, int RB>
+__global__ __launch_bounds__(CSR_THREADS) void k_op_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
+                                                               CsrCtl *__restrict__ wr, int xcd)
+{
+    using V = typename vec2<T>::type;
+    __shared__ CsrCtl nsh;
+    if (!ctl_fold<V, false>(one, rd, wr, nsh, nullptr)) return;
+    op_stage_body<T, RB>(one, &nsh, csr_block(xcd), 2);
+}
+
+template <typename T, int RB> static void op_launch_t(const CsrArgs &a, int what)
+{
+    const dim3 g(a.nblk), t(CSR_THREADS);
+#define QT_ARGS a.insts, a.one, a.ctls, a.bi, a.br, a.xcd, a.bound, what
+    if (a.use_one) {
+        if (what < 2) hipLaunchKernelGGL((k_op<T, RB, true, true>), g, t, 0, a.s, QT_ARGS);
+        else hipLaunchKernelGGL((k_op<T, RB, true, false>), g, t, 0, a.s, QT_ARGS);
+    } else {
+        if (what < 2) hipLaunchKernelGGL((k_op<T, OP_ROWS, false, true>), g, t, 0, a.s, QT_ARGS);
+        else hipLaunchKernelGGL((k_op<T, OP_ROWS, false, false>), g, t, 0, a.s, QT_ARGS);
+    }
+#undef QT_ARGS
+}
+
+template <typename T> static void op_launch(const CsrArgs &a, int what)
+{
+    if (a.use_one && a.one.d <= OP_SMALL_D) op_launch_t<T, OP_ROWS_SMALL>(a, what);
+    else op_launch_t<T, OP_ROWS>(a, what);
+}
+
+template <typename T> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
+{
+    const dim3 g(a.nblk), t(CSR_THREADS);
+    if (a.one.d <= OP_SMALL_D)
+        hipLaunchKernelGGL((k_op_stage2_ctl<T, OP_ROWS_SMALL>), g, t, 0, a.s, a.one, rd, wr, a.xcd);
+    else hipLaunchKernelGGL((k_op_stage2_ctl<T, OP_ROWS>), g, t, 0, a.s, a.one, rd, wr, a.xcd);
+}
+
+void op_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last)
+{
+    for (int what = first; what <= last; ++what) {
+        if (L.f64) op_launch<double>(a, what);
+        else op_launch<float>(a, what);
+    }
+}
+
+void op_stage2_ctl(const CsrLaunch &L, const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
+{
+    if (L.f64) op_ctl<double>(a, rd, wr);
+    else op_ctl<float>(a, rd, wr);
+}
+
+}  // namespace qt

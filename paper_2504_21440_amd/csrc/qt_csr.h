@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qt_op.h"
+
 namespace qt {
 
 // Time-dependent Liouvillians: L(t) = sum_k w_k(t) L_k is stored as one CSR whose rows list the
@@ -66,6 +68,7 @@ struct CsrInst {
     void *cstage;            // [TD_SLOTS][nterms + 1] coefficient values (state precision), column 0 = 1
     // steady-state mode (0: off): stop once |L y|_2^2 <= steady_tol2 after an accepted step
     double steady_tol2;
+    OpForm op;  // operator tables (kernels_op.hip); w = 0: the rows of the matrix are used
 };
 
 // Host: the entry ranges of the first CSR_XOPS of ne expectation operators, from their

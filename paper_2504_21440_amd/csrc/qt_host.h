@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/qtamd.h"
+#include "qt_op.h"
 
 namespace qt {
 
@@ -93,6 +94,10 @@ struct Liouv {
     // time dependence (CSR form): column tags 1..nterms select the coefficient of each entry
     int32_t nterms = 0;
     void *coefs = nullptr;  // device: CoefDev[nterms] followed by their sample tables
+    // operator tables of the staged solver (kernels_op.hip; device pointers into op_mem, op.w = 0: none)
+    OpForm op{};
+    void *op_mem = nullptr;
+    int64_t op_bytes = 0;
     // resident solver (kernels_res.hip): the most generator entries of an element (0: not eligible) and,
     // in the dense form, the upper-triangle ELL a plan or server uploads (res_build_ell)
     int32_t res_w = 0;
@@ -130,6 +135,7 @@ struct CsrLaunch {
     // for the capacity stays valid while the table contents change.
     const int32_t *bound = nullptr, *ibound = nullptr;
     const CsrInst *one_host = nullptr;           // host copy of the descriptor when ninst == 1
+    bool op = false;  // every problem of the launch has operator tables: kernels_op.hip
     bool td = false;  // some problem has a time-dependent Liouvillian: the SpMV kernels weight its terms
     // One problem with runs of 4 stored entries and no steady-state test: the step control
     // is folded into the next step's stage-2 launch (csr_launch_step).

@@ -1,0 +1,42 @@
+// qt_op.h -- operator tables of the staged solver's operator-form right-hand side (kernels_op.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace qt {
+
+constexpr int OP_MAX_W = 12;  // off-diagonal entries per row of A, and collapse operators
+// Below OP_MIN_D the matrix kernels' shorter chain of loads is faster for one problem: a chain of L = 7
+// (d = 128) took 1.97 ms a solve in operator form against 1.62 ms, L = 8 1.97 ms against 2.51 ms.  (From 32 on a
+// problem has no more workgroups (op_blocks) than their default shape has, which is what partial sums and
+// block tables are sized for.)  Up to OP_MAX_D a state's byte offsets have 32 bits.
+constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
+
+// L(rho) = A rho + rho A^dag + sum_c C_c rho C_c^dag from d x d tables (device pointers; w = 0: none).
+// w is the problem's table width, even: entries past a row's own (and channels past the last) are the row
+// itself with value 0 (jumps: column -1).  Kernels index a problem's tables with its own w, never with
+// another's of the same launch.  Every table exists twice, entry by entry over the columns (what 64 lanes
+// read) and row by row (what a wave reads for its rows).
+struct OpForm {
+    int32_t w, pad;
+    const double2 *diag;   // [d] A_ii
+    const int32_t *lcol;   // [w][d] column of A's off-diagonal entry | column of C_c's entry << 16 (0xffff: none)
+    const void *aval;      // [w][d] A's values, state precision
+    const void *cval;      // [w][d] C_c's value, state precision
+    const void *rows;      // [d] records: columns of A [w], of the jumps [w] (-1: none), values of A [w], of the jumps [w]
+};
+
+// Rows one wave serves: fixed by the dimension, so that a problem's sums do not depend on the plan.  Up to
+// d = 256 one problem does not fill the chip and the latency of a wave counts (one chain of L = 8: 4.3 ms a solve
+// with one row, 5.4 ms with two); above, the vector L1 (L = 10, complex128: 14.2 ms and 12.4 ms).
+constexpr int OP_ROWS = 2, OP_ROWS_SMALL = 1, OP_SMALL_D = 256;
+__host__ __device__ inline int op_rows(int d) { return d > OP_SMALL_D ? OP_ROWS : OP_ROWS_SMALL; }
+
+// Workgroups of a problem: the 64 x 64 tiles of the upper triangle, each cut into groups of four waves' rows.
+__host__ __device__ inline int op_blocks(int d)
+{
+    const int t = (d + 63) / 64;
+    return t * (t + 1) / 2 * (16 / op_rows(d));
+}
+
+}  // namespace qt

@@ -60,6 +60,7 @@ qt_status res_launch(int cls, bool f64, const ResInst *insts, ResCtl *ctls, cons
                      int count, int max_steps_launch, int reset, hipStream_t s);
 
 // ---- host side of plans and servers (qtamd_me.cpp) ----
+bool exactly_hermitian(int32_t d, const double *rho0);
 bool res_problem(const Liouv &L, bool dense, const double *rho0);
 void res_fill_inst(ResInst *g, const Liouv &L, bool dense, int nt, int ne, const void *rho0, void *vec,
                    const double *tlist, const int32_t *eptr, const int32_t *evidx, const double2 *eval,

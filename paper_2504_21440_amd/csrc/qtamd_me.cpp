@@ -29,6 +29,7 @@ struct MeProb {
     bool dense = false;
     int32_t slot = -1;  // index inside its group
     int32_t res = -1;   // index among the resident problems (kernels_res.hip), -1: not one
+    bool op = false;    // CSR form run by the operator-form kernels (kernels_op.hip) unless resident
     size_t o_rho0 = 0, o_tlist = 0, o_eptr = 0, o_ecol = 0, o_eval = 0, o_evidx = 0, o_expect = 0;
     size_t o_vec = 0;  // state vectors
     size_t o_part = 0;
@@ -65,6 +66,7 @@ struct qt_me_plan {
         std::vector<int32_t> members;  // CSR problem slots
         int32_t boff = 0, nblk = 0;    // block-table segment
         int32_t ioff = 0;              // control-list segment
+        bool op = false;               // problems with operator tables, run by the operator-form kernels
         bool listed = false;           // false: the control launch visits problems 0 .. ncsr-1
         hipStream_t stream = nullptr;
         hipGraph_t graph = nullptr;
@@ -94,7 +96,7 @@ struct qt_me_plan {
     qt::ResCtl *h_rctl = nullptr;  // pinned
     std::vector<Bucket> rbuckets;  // np: kernel class
     bool res_stale = false;        // the ELLs of dense-form problems have been overwritten
-    bool lanes_all = true;         // the lanes hold the resident problems too (timing)
+    bool lanes_all = false;        // every CSR problem in one lane of matrix kernels (timing)
     double last_ms = 0.0;
     bool counted = false;  // holds a reference on ctx
 };
@@ -129,6 +131,20 @@ size_t res_ell_offset(int d, int prec)
 }
 size_t res_ell_bytes(const Liouv &L) { return L.res_val.size() * (state_es(L.precision) + 4); }
 
+// rho0_ij == conj(rho0_ji) for every element (in tiles: a row against a column of a large state)
+bool exactly_hermitian(int32_t d, const double *rho0)
+{
+    constexpr int32_t B = 32;
+    for (int32_t ib = 0; ib < d; ib += B)
+        for (int32_t jb = ib; jb < d; jb += B)
+            for (int32_t i = ib; i < std::min(ib + B, d); ++i)
+                for (int32_t j = std::max(i, jb); j < std::min(jb + B, d); ++j) {
+                    const size_t a = 2 * ((size_t)i * d + j), b = 2 * ((size_t)j * d + i);
+                    if (rho0[a] != rho0[b] || rho0[a + 1] != -rho0[b + 1]) return false;
+                }
+    return true;
+}
+
 // The resident kernel takes a constant generator of few entries per element whose initial state is
 // exactly Hermitian (the dense form integrates the Hermitian part anyway); a dense-form problem's
 // ELL has to fit beside the state in the vectors the matrix-core solver would use.
@@ -138,12 +154,7 @@ bool res_problem(const Liouv &L, bool dense, const double *rho0)
     const int32_t d = L.d;
     if (dense) return res_ell_offset(d, L.precision) + res_ell_bytes(L) <=
                       dense_state_vectors() * (size_t)dense_np(d) * dense_np(d) * state_es(L.precision);
-    for (int32_t i = 0; i < d; ++i)
-        for (int32_t j = i; j < d; ++j) {
-            const size_t a = 2 * ((size_t)i * d + j), b = 2 * ((size_t)j * d + i);
-            if (rho0[a] != rho0[b] || rho0[a + 1] != -rho0[b + 1]) return false;
-        }
-    return true;
+    return exactly_hermitian(d, rho0);
 }
 
 // Fills a resident descriptor (vec: the problem's state vectors).
@@ -253,6 +264,7 @@ static qt_status prep_problem(const qt_me_problem &p, int32_t prec, MeProb *m)
         for (size_t i = 0; i < 2 * n; ++i) f[i] = (float)r[i];
     }
     m->res = res_problem(*p.L, m->dense, r.data()) ? 0 : -1;
+    m->op = p.L->op.w > 0 && exactly_hermitian(d, r.data());
     // e_ops as concatenated int32 CSR (instance-local offsets)
     m->eptr.assign((size_t)p.n_e * (d + 1), 0);
     m->ecol.clear();
@@ -295,15 +307,16 @@ static qt_status layout_lanes(qt_me_plan *P)
     std::vector<int32_t> bi, br, il;
     for (auto &l : P->lanes) {
         drop_graph(l);
-        if (l.done) continue;
+        if (l.done || l.members.empty()) continue;
         l.boff = (int32_t)bi.size();
         l.ioff = (int32_t)il.size();
         for (int32_t i : l.members) {
             CsrInst &c = P->h_ci[i];
             c.block0 = (int32_t)bi.size();
+            c.nblocks = l.op ? op_blocks(c.d) : (c.n + rpb - 1) / rpb;
             for (int32_t b = 0; b < c.nblocks; ++b) {
                 bi.push_back(i);
-                br.push_back(b * rpb);
+                br.push_back(l.op ? b : b * rpb);
             }
             il.push_back(i);
         }
@@ -325,13 +338,24 @@ static qt_status reset_lanes(qt_me_plan *P)
 {
     for (auto &l : P->lanes) drop_graph(l);
     P->lanes.assign(1, qt_me_plan::Lane{});
-    auto &l = P->lanes[0];
-    // resident problems have no launches of their own in a run, only in the stage timing
-    for (auto &m : P->probs)
-        if (!m.dense && (P->lanes_all || m.res < 0)) l.members.push_back(m.slot);
-    l.listed = (int32_t)l.members.size() < P->ncsr;
-    l.done = l.members.empty();
-    l.stream = P->ctx->stream;
+    // resident problems have no launches of their own in a run, and problems with operator tables have a
+    // lane of their own; the stage timing takes every problem through the matrix kernels
+    qt_me_plan::Lane ops;
+    ops.op = true;
+    for (auto &m : P->probs) {
+        if (m.dense || (!P->lanes_all && m.res >= 0)) continue;
+        if (!P->lanes_all && m.op) ops.members.push_back(m.slot);
+        else P->lanes[0].members.push_back(m.slot);
+    }
+    if (!ops.members.empty()) {
+        if (P->lanes[0].members.empty()) P->lanes[0] = ops;
+        else P->lanes.push_back(ops);
+    }
+    for (auto &l : P->lanes) {
+        l.listed = (int32_t)l.members.size() < P->ncsr;
+        l.done = l.members.empty();
+        l.stream = P->ctx->stream;
+    }
     P->split = false;
     return layout_lanes(P);
 }
@@ -340,8 +364,6 @@ static qt_status reset_lanes(qt_me_plan *P)
 static qt_status apply_shape(qt_me_plan *P, CsrShape sh)
 {
     if (!csr_shape_supported(sh.lpr, sh.rg, sh.keep)) return set_error(QT_EINVAL, "unsupported CSR tile shape");
-    const int rpb = csr_rows_per_block(sh.lpr, sh.rg);
-    for (int32_t i = 0; i < P->ncsr; ++i) P->h_ci[i].nblocks = (P->h_ci[i].n + rpb - 1) / rpb;
     P->shape = sh;
     return reset_lanes(P);
 }
@@ -350,7 +372,6 @@ static qt_status apply_shape(qt_me_plan *P, CsrShape sh)
 // finished keeps its layout and graph.
 static qt_status restore_full(qt_me_plan *P, bool all)
 {
-    all = all || P->nres == 0;
     if (P->split || all != P->lanes_all) {
         P->lanes_all = all;
         return reset_lanes(P);
@@ -445,7 +466,6 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
         P->o_rinst = A.reserve(sizeof(ResInst) * P->nres);
         P->o_rctl = A.reserve(sizeof(ResCtl) * P->nres);
         P->o_rorder = A.reserve(sizeof(int32_t) * P->nres);
-        P->lanes_all = false;
     }
     if (query) {
         *query = A.size;
@@ -508,6 +528,7 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
             c.partials = (double *)A.at(m.o_part);
             csr_set_expect_ranges(c, m.eptr.data(), m.ne, m.d);
             c.steady_tol2 = steady_tol * steady_tol;
+            if (m.op) c.op = m.L->op;
             if (P->td) {
                 // every CSR problem of the plan takes the weighted kernels; a constant one has only
                 // the column of ones
@@ -626,9 +647,14 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
 // Whether a step's control folds into the next step's stage-2 launch at matrix load kind keep: one
 // problem stored in runs of 4 entries (keep 2) with no steady-state test, over an even number of
 // steps per graph (the double-buffered record ends where it began).
+// Every workgroup of the folded launch reads every block partial, so a problem of very many blocks keeps
+// the control launch: 32,768 blocks (L = 10, FP64, matrix kernels) took 259 us folded against 118 + 18 us;
+// 1,088 blocks (the same problem in operator form) 35 us against 28 + 12 us.
+constexpr int32_t FOLD_MAX_BLOCKS = 8192;
 static bool folds_control(const qt_me_plan *P, int keep)
 {
-    return P->ncsr == 1 && keep == 2 && P->h_ci[0].steady_tol2 <= 0.0 && P->graph_steps % 2 == 0;
+    return P->ncsr == 1 && keep == 2 && P->h_ci[0].steady_tol2 <= 0.0 && P->graph_steps % 2 == 0 &&
+           P->h_ci[0].nblocks <= FOLD_MAX_BLOCKS;
 }
 
 static CsrLaunch csr_args(const qt_me_plan *P, int k = 0)
@@ -650,6 +676,11 @@ static CsrLaunch csr_args(const qt_me_plan *P, int k = 0)
     L.one_host = P->ncsr == 1 ? &P->h_ci[0] : nullptr;
     L.td = P->td;
     L.fused = folds_control(P, P->shape.keep);
+    if (l.op) {
+        L.op = true;
+        L.xcd = 1;  // a problem's rows share an L2: 16 chains of L = 8 miss it half as often
+        L.fused = folds_control(P, 2);
+    }
     return L;
 }
 
@@ -733,13 +764,16 @@ qt_status me_plan_run(qt_me_plan *P)
     qt_status st = QT_OK;
     if (nstaged) {
         if ((st = restore_full(P, false))) return st;
-        const CsrLaunch L = csr_args(P, 0);
-        auto *cc = L.ctls;
-        csr_launch_reset(L.insts, L.ctls, P->ncsr, L.f64, s);
-        csr_launch_init(0, L, s);
-        csr_launch_init(1, L, s);
-        QT_HIP(hipGetLastError());
-        if ((st = capture_graph(P, 0))) return st;
+        auto *cc = (CsrCtl *)P->arena.at(P->o_cctl);
+        csr_launch_reset((const CsrInst *)P->arena.at(P->o_cinst), cc, P->ncsr, P->prec == QT_F64, s);
+        for (size_t k = 0; k < P->lanes.size(); ++k) {
+            if (P->lanes[k].done) continue;
+            const CsrLaunch L = csr_args(P, (int)k);
+            csr_launch_init(0, L, s);
+            csr_launch_init(1, L, s);
+            QT_HIP(hipGetLastError());
+            if ((st = capture_graph(P, (int)k))) return st;
+        }
         int64_t last_steps = -1;
         std::vector<double> rem(P->ncsr, 0.0);  // steps still needed, from the current step size
         for (;;) {
@@ -811,6 +845,7 @@ qt_status me_plan_run(qt_me_plan *P)
                         qt_me_plan::Lane nlane;
                         nlane.members = slow;
                         nlane.listed = true;
+                        nlane.op = P->lanes[k].op;
                         nlane.stream = P->lane_streams[j];
                         P->lanes[k].members = rest;  // (reference l may move with the push_back)
                         P->lanes[k].listed = true;

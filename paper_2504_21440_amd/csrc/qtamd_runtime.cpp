@@ -505,6 +505,75 @@ static qt_status assemble_csr(Ctx *ctx, const HCsr &A, const HCsr *B, const std:
     return QT_OK;
 }
 
+// Operator tables of a constant CSR-form Liouvillian for the staged solver (qt_op.h), if its operators have
+// the form: at most OP_MAX_W off-diagonal entries per row of A and channels, at most one entry per row of
+// every C_k.  Then an element takes at most 3 OP_MAX_W + 1 sources of 8 or 16 bytes, most of them from the
+// caches, where the assembled matrix streams 12 or 20 bytes for each from memory; a channel of more entries
+// per row would need their products, which the matrix holds summed.
+static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int32_t prec, Liouv *L)
+{
+    const int32_t d = A.d, nc = (int32_t)cs.size();
+    if (d < OP_MIN_D || d > OP_MAX_D || nc > OP_MAX_W) return QT_OK;
+    int w = std::max(1, nc);
+    for (int32_t i = 0; i < d; ++i) {
+        int k = 0;
+        for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) k += A.idx[p] != i;
+        w = std::max(w, k);
+        for (const HCsr &c : cs)
+            if (c.ptr[i + 1] - c.ptr[i] > 1) return QT_OK;
+    }
+    if (w > OP_MAX_W) return QT_OK;
+    w = (w + 1) & ~1;
+    const size_t es = prec == QT_F64 ? 16 : 8, rec = (size_t)w * (8 + 2 * es);
+    auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+    const size_t o_lc = up((size_t)d * 16), o_av = o_lc + up((size_t)w * d * 4), o_cv = o_av + up((size_t)w * d * es),
+                 o_rec = o_cv + up((size_t)w * d * es), total = o_rec + up((size_t)d * rec);
+    std::vector<char> h(total, 0);
+    double2 *diag = (double2 *)h.data();
+    int32_t *lc = (int32_t *)(h.data() + o_lc);
+    auto put = [&](size_t base, size_t k, cd v) {
+        if (prec == QT_F64) ((double2 *)(h.data() + base))[k] = make_double2(v.real(), v.imag());
+        else ((float2 *)(h.data() + base))[k] = make_float2((float)v.real(), (float)v.imag());
+    };
+    for (int32_t i = 0; i < d; ++i) {
+        const size_t r = o_rec + (size_t)i * rec;
+        int32_t *rac = (int32_t *)(h.data() + r), *rcc = rac + w;
+        const size_t rav = r + 8 * (size_t)w, rcv = rav + (size_t)w * es;
+        int k = 0;
+        for (int64_t p = A.ptr[i]; p < A.ptr[i + 1]; ++p) {
+            if (A.idx[p] == i) {
+                diag[i] = make_double2(A.val[p].real(), A.val[p].imag());
+                continue;
+            }
+            rac[k] = lc[(size_t)k * d + i] = A.idx[p];
+            put(o_av, (size_t)k * d + i, A.val[p]);
+            put(rav, k, A.val[p]);
+            ++k;
+        }
+        for (; k < w; ++k) rac[k] = lc[(size_t)k * d + i] = i;
+        for (int32_t c = 0; c < w; ++c) {
+            const bool has = c < nc && cs[c].ptr[i + 1] > cs[c].ptr[i];
+            rcc[c] = has ? cs[c].idx[cs[c].ptr[i]] : -1;
+            lc[(size_t)c * d + i] |= (int32_t)((uint32_t)(has ? rcc[c] : 0xffff) << 16);
+            if (!has) continue;
+            put(o_cv, (size_t)c * d + i, cs[c].val[cs[c].ptr[i]]);
+            put(rcv, c, cs[c].val[cs[c].ptr[i]]);
+        }
+    }
+    if (hipMalloc(&L->op_mem, total) != hipSuccess) return set_error(QT_ENOMEM, "hipMalloc operator tables");
+    if (hipMemcpy(L->op_mem, h.data(), total, hipMemcpyHostToDevice) != hipSuccess)
+        return set_error(QT_EDEVICE, "upload operator tables");
+    L->op_bytes = (int64_t)total;
+    const char *b = (const char *)L->op_mem;
+    L->op.w = w;
+    L->op.diag = (const double2 *)b;
+    L->op.lcol = (const int32_t *)(b + o_lc);
+    L->op.aval = b + o_av;
+    L->op.cval = b + o_cv;
+    L->op.rows = b + o_rec;
+    return QT_OK;
+}
+
 qt_status qt_liouvillian_build(qt_ctx *ctx, const qt_csr *H, int32_t n_c, const qt_csr *c_ops, int32_t form,
                                int32_t precision, qt_liouv **out)
 {
@@ -583,6 +652,11 @@ qt_status qt_liouvillian_build(qt_ctx *ctx, const qt_csr *H, int32_t n_c, const 
     }
     const int64_t n = (int64_t)d * d;
     L->bytes = (int64_t)((n + 1) * 4 + L->nnz_stored * (4 + (int64_t)es));
+    if ((st = build_op_tables(A, cs, precision, L))) {
+        ctx->refs++;
+        qt_liouv_destroy(L);
+        return st;
+    }
     ctx->refs++, *out = L;
     return QT_OK;
 }
@@ -793,14 +867,14 @@ qt_status qt_liouv_info(const qt_liouv *L, int32_t *d, int64_t *nnz, int64_t *by
     if (!L) return set_error(QT_EINVAL, "null Liouvillian");
     if (d) *d = L->d;
     if (nnz) *nnz = L->nnz;
-    if (bytes) *bytes = L->bytes;
+    if (bytes) *bytes = L->bytes + L->op_bytes;
     return QT_OK;
 }
 
 qt_status qt_liouv_footprint(const qt_liouv *L, size_t *bytes)
 {
     if (!L || !bytes) return set_error(QT_EINVAL, "qt_liouv_footprint: null argument");
-    *bytes = (size_t)L->bytes;
+    *bytes = (size_t)(L->bytes + L->op_bytes);
     return QT_OK;
 }
 
@@ -848,6 +922,7 @@ qt_status qt_liouv_destroy(qt_liouv *L)
     if (L->val) (void)hipFree(L->val);
     if (L->dense) (void)hipFree(L->dense);
     if (L->coefs) (void)hipFree(L->coefs);
+    if (L->op_mem) (void)hipFree(L->op_mem);
     L->ctx->refs--;
     delete L;
     return QT_OK;

@@ -83,6 +83,7 @@ struct Request {
     uint64_t ticket = 0;
     int32_t slot = -1;
     bool dense = false;
+    bool op = false;   // run by the operator-form kernels
     int32_t res = -1;  // kernel class of a resident request (kernels_res.hip), -1: not one
     int32_t d = 0, nt = 0, ne = 0, np = 0;
     size_t off = 0, bytes = 0;
@@ -128,7 +129,9 @@ struct qt_server {
         size_t blk_cap = 0;           // entries of d_bi / d_br (a power of two, fixed at creation)
         std::map<int, EpochGraph> graphs;
     };
-    Lane lanes[2];  // 0: large Liouvillians (context stream), 1: small ones (auxiliary stream)
+    // 0: large Liouvillians (context stream), 1: small ones (auxiliary stream); 2, 3: the same of the requests
+    // that the operator-form kernels run
+    Lane lanes[4];
     qt::CsrCtl *h_cctl = nullptr;   // pinned
     qt::DenseCtl *h_dctl = nullptr; // pinned
     qt::ResCtl *h_rctl = nullptr;   // pinned
@@ -261,6 +264,7 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
     up(Ly.o_evidx, evidx.data(), evidx.size() * 4);
     qt_opts o = S->cfg.opts;
     const int rescls = res_problem(*p->L, dense, r.data()) ? res_class(d, p->L->res_w, p->L->res_band, S->prec) : -1;
+    const bool op = rescls < 0 && !dense && p->L->op.w > 0 && exactly_hermitian(d, r.data());
     ResInst ri;
     std::vector<char> ell;  // alive until the uploads are waited for
     if (rescls >= 0) {
@@ -296,6 +300,10 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
         c.nt = p->n_t;
         c.ne = p->n_e;
         c.block0 = 0;  // not used by the kernels (a block finds its partial slot from its first row)
+        if (op) {
+            c.op = p->L->op;
+            nblocks = op_blocks(d);  // no more than the matrix kernels': the partials and the table fit
+        }
         c.nblocks = nblocks;
         c.renorm = S->prec == QT_MIXED ? 1 : 0;
         c.use_h0 = o.h0 > 0 ? 1 : 0;
@@ -347,6 +355,7 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
     R.slot = slot;
     R.dense = dense;
     R.res = rescls;
+    R.op = op;
     R.d = d;
     R.nt = p->n_t;
     R.ne = p->n_e;
@@ -377,8 +386,10 @@ constexpr int64_t SMALL_LANE_ROWS = 16384;
 
 // Uploads a lane's block table and control list and launches its epoch graph (capturing it on
 // first use of this grid size) on stream s.
+// op: run by the operator-form kernels.
 static qt_status launch_lane(qt_server *S, qt_server::Lane &ln, const std::vector<int32_t> &bi,
-                             const std::vector<int32_t> &br, const std::vector<int32_t> &slots, int K, hipStream_t s)
+                             const std::vector<int32_t> &br, const std::vector<int32_t> &slots, int K, bool op,
+                             hipStream_t s)
 {
     int grid = 256;
     while ((size_t)grid < bi.size()) grid *= 2;
@@ -398,6 +409,7 @@ static qt_status launch_lane(qt_server *S, qt_server::Lane &ln, const std::vecto
         L.rg = S->shape.rg;
         L.xcd = 0;
         L.keep = S->shape.keep;
+        L.op = op;
         L.nblk = grid;               // blocks past the live count return at once
         L.ninst = S->cfg.max_slots;  // likewise for the control list
         L.ilist = ln.d_ilist;
@@ -436,15 +448,15 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     const bool f64 = S->prec == QT_F64;
     const int K = std::max(1, S->cfg.steps_per_epoch);
     // ---- CSR slots: one block table per lane ----
-    std::vector<int32_t> bi[2], br[2], csr_slots[2];
+    std::vector<int32_t> bi[4], br[4], csr_slots[4];
     const int rpb = csr_rows_per_block(S->shape.lpr, S->shape.rg);
     for (uint64_t tk : S->active) {
         Request &R = S->reqs[tk];
         if (R.dense || R.res >= 0) continue;
-        const int l = (int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0;
+        const int l = ((int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0) + (R.op ? 2 : 0);
         for (int32_t b = 0; b < R.nblocks; ++b) {
             bi[l].push_back(R.slot);
-            br[l].push_back(b * rpb);
+            br[l].push_back(R.op ? b : b * rpb);
         }
         csr_slots[l].push_back(R.slot);
     }
@@ -492,8 +504,10 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     const bool mfma = !buckets.empty();
     // ---- large CSR lane (after the dense launches' start event, so those run beside it) ----
     hipEvent_t big_done = nullptr;
-    if (!bi[0].empty()) {
-        qt_status st = launch_lane(S, S->lanes[0], bi[0], br[0], csr_slots[0], K, s);
+    if (!bi[0].empty() || !bi[2].empty()) {
+        qt_status st = QT_OK;
+        for (int l : {0, 2})
+            if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l >= 2, s);
         if (st) {
             if (ev) (void)hipEventDestroy(ev);
             return st;
@@ -502,7 +516,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
         QT_HIP(hipEventRecord(big_done, s));
     }
     // ---- small CSR lane and resident requests: replayed while the large lane runs and one of them still steps ----
-    if (!bi[1].empty() || !rruns.empty()) {
+    if (!bi[1].empty() || !bi[3].empty() || !rruns.empty()) {
         hipStream_t sa = ctx->aux;
         constexpr int MAX_REPLAYS = 64;  // bounds an epoch, so that new requests are admitted
         qt_status st = QT_OK;
@@ -511,12 +525,10 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
             for (size_t k = 0; k < rruns.size() && !st; ++k)
                 st = res_launch(rruns[k].cls, f64, S->d_rinst, S->d_rctl, S->d_order + rruns[k].start, rruns[k].count,
                                 K, 0, ctx->pool[(buckets.size() + k) % Ctx::NPOOL]);
-            if (!st && !bi[1].empty()) {
-                st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, sa);
-                if (!st)
-                    e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots,
-                                       hipMemcpyDeviceToHost, sa);
-            }
+            for (int l : {1, 3})
+                if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l >= 2, sa);
+            if (!st && (!bi[1].empty() || !bi[3].empty()))
+                e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
             if (!rruns.empty())
                 for (int b = 0; b < Ctx::NPOOL && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[b]);
             if (!st && e == hipSuccess && !rruns.empty())
@@ -524,7 +536,8 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
             if (e == hipSuccess) e = hipStreamSynchronize(sa);
             if (!big_done || hipEventQuery(big_done) != hipErrorNotReady) break;
             bool running = false;
-            for (int32_t slot : csr_slots[1]) running = running || S->h_cctl[slot].status == ST_RUNNING;
+            for (int l : {1, 3})
+                for (int32_t slot : csr_slots[l]) running = running || S->h_cctl[slot].status == ST_RUNNING;
             for (auto &x : rlist) running = running || S->h_rctl[S->reqs[x.second].slot].status == ST_RUNNING;
             if (!running) break;
         }
@@ -628,7 +641,7 @@ static qt_status check_cfg(const qt_server_cfg *cfg)
 
 // Lays out the server's device memory in S->arena and returns the offsets through the members.
 struct ServerLayout {
-    size_t pool, cinst, cctl, dinst, dctl, order, rinst, rctl, ilist[2], counts[2], bi[2], br[2];
+    size_t pool, cinst, cctl, dinst, dctl, order, rinst, rctl, ilist[4], counts[4], bi[4], br[4];
 };
 static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap)
 {
@@ -642,7 +655,7 @@ static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap
     L.order = A.reserve(sizeof(int32_t) * ns);
     L.rinst = A.reserve(sizeof(ResInst) * ns);
     L.rctl = A.reserve(sizeof(ResCtl) * ns);
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 4; ++k) {
         L.ilist[k] = A.reserve(sizeof(int32_t) * ns);
         L.counts[k] = A.reserve(sizeof(int32_t) * 2);
         L.bi[k] = A.reserve(4 * cap);
@@ -678,7 +691,7 @@ static qt_status server_create(Ctx *ctx, const qt_server_cfg *cfg, void *ws, siz
     S->d_order = (int32_t *)A.at(Ly.order);
     S->d_rinst = (ResInst *)A.at(Ly.rinst);
     S->d_rctl = (ResCtl *)A.at(Ly.rctl);
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 4; ++k) {
         auto &ln = S->lanes[k];
         ln.d_ilist = (int32_t *)A.at(Ly.ilist[k]);
         ln.d_counts = (int32_t *)A.at(Ly.counts[k]);
