@@ -11,13 +11,15 @@
 // above the diagonal are evaluated, and a workgroup writes its elements and, transposed through LDS, their
 // conjugates below: half the sums and half the reads of the epilogue.
 //
-// What bounds it: one chain of L = 8 (complex64, 160 workgroups) the latency of a wave, kernel by kernel --
-// 5.0 us a stage, of which the launch is about 2 -- so there a wave takes one row and requests every source
-// before the first sum; with two rows it took 6.1 us, with the sources requested as they are used 5.3 us.
+// What bounds it: one chain of L = 8 (160 workgroups) the latency of a wave, kernel by kernel -- 4.8 us a stage in
+// complex64, of which the launch is about 2 -- so there a wave takes one row, the descriptor, the control record
+// and the column's entries are requested together, and every source before the first sum; with descriptor
+// words read where they are used it took 5.0 us (a solve 4.29 ms against 4.14, in complex128 4.05 against
+// 3.66 ms), with two rows 6.1 us.
 // L = 10 (complex128) the vector L1: 30 sources and 20 table words per element at 4 lanes a cycle are 12 us,
 // beside 130 MB of state vectors from the L2s and the MALL; 28 us a stage (118 us for the matrix kernels, which
 // stream 531 MB; 40 us without the Hermitian halving).  Two rows a wave read each column entry for two
-// elements; four rows took 40 us (too few waves in flight), one row 33 us.  Sixteen chains of L = 8: 19 us a
+// elements; four rows took 40 us (too few waves in flight), one row 33 us.  Sixteen chains of L = 8: 20 us a
 // stage against 45 to 60 us.
 //
 // The diagonal is formed in FP64 and rounded once, as the assembled matrix holds it.  Everything else of a
@@ -114,49 +116,77 @@ __device__ __forceinline__ void op_mirror(const OpMirror<V, RB> &sh, const OpIte
     }
 }
 
+// A wave-uniform value in scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uniform(double v)
+{
+    return __hiloint2double(uniform(__double2hiint(v)), uniform(__double2loint(v)));
+}
+
+// Keeps a uniform value where it is read: the compiler would otherwise move each read of a descriptor to its
+// first use, one round trip to memory after the other.
+template <typename P> __device__ __forceinline__ void keep(P &p) { asm volatile("" : "+s"(p)); }
+
+// A problem's tables, read from its descriptor at once.
+struct OpTabs {
+    int w;
+    const double2 *diag;
+    const int32_t *lcol;
+    const void *aval, *cval, *rows;
+    __device__ __forceinline__ explicit OpTabs(const OpForm &O)
+        : w(O.w), diag(O.diag), lcol(O.lcol), aval(O.aval), cval(O.cval), rows(O.rows)
+    {
+        keep(w), keep(diag), keep(lcol), keep(aval), keep(cval), keep(rows);
+    }
+};
+
+// M entries of this lane's column, from entry k on.
+template <typename V, int M> struct OpCols {
+    V a[M], c[M];   // conj A_jl; C_c's value
+    uint32_t l[M];  // their columns
+    __device__ __forceinline__ void load(const OpTabs &O, int d, int j, int k)
+    {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const uint32_t q = (uint32_t)((k + m) * d + j);
+            l[m] = (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u));
+            a[m] = at((const V *)O.aval, q * (uint32_t)sizeof(V));
+            a[m].y = -a[m].y;
+            c[m] = at((const V *)O.cval, q * (uint32_t)sizeof(V));
+        }
+    }
+};
+
 // L x at the wave's RB rows in this lane's column; x(o) is the input at byte offset o.  The loops run over
-// the entries, four at a time for all rows: 4 RB sources are in flight at once, a column's entries are read
-// once for the RB rows, and nothing but the sums stays in registers.
-template <typename T, int RB, typename X>
-__device__ __forceinline__ void op_sum(const OpForm &O, int d, const OpItem<RB> &it, X x,
+// the entries, a few at a time for all rows: a column's entries are read once for the RB rows, and nothing but
+// the sums stays in registers.  pre: the first M0 entries (the first group).  One row (small problems, bound
+// by the latency of a wave): every source of a group is requested before its first sum; more: up to four
+// entries of RB rows in flight.
+template <typename T, int RB, int M0, typename X>
+__device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> &it, double2 dj,
+                                       const OpCols<typename vec2<T>::type, M0> &pre, X x,
                                        typename vec2<T>::type (&acc)[RB])
 {
     using V = typename vec2<T>::type;
     constexpr uint32_t ES = sizeof(V);
     const int w = O.w;
     const uint32_t ds = (uint32_t)d * ES, jo = (uint32_t)it.j * ES;
-    const V *__restrict__ aval = uniform_ptr((const V *)O.aval);
-    const V *__restrict__ cval = uniform_ptr((const V *)O.cval);
-    const int32_t *__restrict__ lcol = uniform_ptr(O.lcol);
     const int32_t *rac[RB];
     const V *rav[RB];
-    const double2 dj = gld(O.diag + it.j);
+    V own[RB];
+    double2 di[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-        const char *rec = uniform_ptr((const char *)O.rows) + (size_t)it.i[r] * ((size_t)w * (8 + 2 * ES));
+        const char *rec = (const char *)O.rows + (uint32_t)(it.i[r] * w) * (uint32_t)(8 + 2 * ES);
         rac[r] = (const int32_t *)rec;              // [w] columns of A, [w] columns of the jumps
         rav[r] = (const V *)(rec + 8 * (size_t)w);  // [w] values of A, [w] of the jumps
-        const double2 di = uld(O.diag + it.i[r]);
-        V dd;
-        dd.x = (T)(di.x + dj.x);
-        dd.y = (T)(di.y - dj.y);
-        acc[r].x = acc[r].y = T(0);
-        cfma(acc[r], dd, x((uint32_t)it.i[r] * ds + jo));
+        di[r] = uld(O.diag + it.i[r]);
+        own[r] = x((uint32_t)it.i[r] * ds + jo);
     }
-    // M entries at a time for all rows.  One row (small problems, bound by the latency of a wave): every source
-    // is requested before the first sum; more: up to M RB sources in flight.
-    auto part = [&](auto count, int k) {
-        constexpr int M = decltype(count)::value;
-        V a[M], c[M], up[RB][M], side[RB][M], jump[RB][M];
-        uint32_t l[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const uint32_t q = (uint32_t)((k + m) * d + it.j);
-            l[m] = (uint32_t)gld(lcol + q);
-            a[m] = at(aval, q * ES);
-            a[m].y = -a[m].y;
-            c[m] = at(cval, q * ES);
-        }
+    auto part = [&](auto first, const auto &col, int k) {
+        constexpr int M = sizeof(col.l) / 4;
+        constexpr bool FIRST = decltype(first)::value;
+        V up[RB][M], side[RB][M], jump[RB][M];
         // A rho: the column's other rows
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -166,7 +196,7 @@ __device__ __forceinline__ void op_sum(const OpForm &O, int d, const OpItem<RB> 
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
-                for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (l[m] & 0xffffu) * ES);
+                for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (col.l[m] & 0xffffu) * ES);
         };
         auto load_jump = [&]() {  // the jumps; an element without one takes itself, times zero
 #pragma unroll
@@ -174,42 +204,62 @@ __device__ __forceinline__ void op_sum(const OpForm &O, int d, const OpItem<RB> 
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
                     const int ki = uld(rac[r] + w + k + m);
-                    const bool has = ki >= 0 && (l[m] >> 16) != 0xffffu;
-                    jump[r][m] = x(has ? (uint32_t)ki * ds + (l[m] >> 16) * ES : (uint32_t)it.i[r] * ds + jo);
+                    const uint32_t own_o = (uint32_t)it.i[r] * ds + jo, o = (uint32_t)ki * ds + (col.l[m] >> 16) * ES;
+                    const uint32_t none = (uint32_t)(ki >> 31) | (uint32_t)((int32_t)(col.l[m] >> 16 ^ 0xffffu) - 1 >> 31);
+                    jump[r][m] = x(o ^ ((o ^ own_o) & none));  // (bit operations: a select became a branch)
                 }
         };
+        V va[RB][M], vc[RB][M];
         if constexpr (RB == 1) {
             load_side();
             load_jump();
+#pragma unroll
+            for (int m = 0; m < M; ++m) va[0][m] = uld(rav[0] + k + m), vc[0][m] = uld(rav[0] + w + k + m);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (FIRST) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                V dd;
+                dd.x = (T)(di[r].x + dj.x);
+                dd.y = (T)(di[r].y - dj.y);
+                acc[r].x = acc[r].y = T(0);
+                cfma(acc[r], dd, own[r]);
+            }
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int m = 0; m < M; ++m) cfma(acc[r], uld(rav[r] + k + m), up[r][m]);
+            for (int m = 0; m < M; ++m) cfma(acc[r], RB == 1 ? va[r][m] : uld(rav[r] + k + m), up[r][m]);
         if constexpr (RB > 1) load_side();
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int m = 0; m < M; ++m) cfma(acc[r], a[m], side[r][m]);
+            for (int m = 0; m < M; ++m) cfma(acc[r], col.a[m], side[r][m]);
         if constexpr (RB > 1) load_jump();
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int m = 0; m < M; ++m) cfma(acc[r], cmulc(uld(rav[r] + w + k + m), c[m]), jump[r][m]);
+            for (int m = 0; m < M; ++m)
+                cfma(acc[r], cmulc(RB == 1 ? vc[r][m] : uld(rav[r] + w + k + m), col.c[m]), jump[r][m]);
     };
-    int k = 0;
-    if constexpr (RB == 1) {
+    part(std::true_type{}, pre, 0);
+    int k = M0;
 #pragma unroll 1
-        for (; k + 8 <= w; k += 8) part(std::integral_constant<int, 8>{}, k);
+    for (; k + 4 <= w; k += 4) {
+        OpCols<V, 4> col;
+        col.load(O, d, it.j, k);
+        part(std::false_type{}, col, k);
     }
-#pragma unroll 1
-    for (; k + 4 <= w; k += 4) part(std::integral_constant<int, 4>{}, k);
-    if (k < w) part(std::integral_constant<int, 2>{}, k);
+    if (k < w) {
+        OpCols<V, 2> col;
+        col.load(O, d, it.j, k);
+        part(std::false_type{}, col, k);
+    }
 }
 
 // Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.
-template <typename T, int RB>
+template <typename T, int RB, int M0>
 __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, int blk, int which)
 {
     using V = typename vec2<T>::type;
@@ -224,16 +274,20 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
     V *__restrict__ y = uniform_ptr((V *)I.Y[0]);
     V *__restrict__ k1 = uniform_ptr((V *)I.K[0]);
     double sa = 0.0, sb = 0.0;
+    const OpTabs O(I.op);
     if (it.i0 < d) {
+        OpCols<V, M0> pre;
+        pre.load(O, d, it.j, 0);
+        const double2 dj = gld(O.diag + it.j);
         V acc[RB];
         if (which)
-            op_sum<T, RB>(I.op, d, it, [&](uint32_t o) {
+            op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) {
                 V v = at((const V *)y, o);
                 caxpy(v, th0, at((const V *)k1, o));
                 return v;
             }, acc);
         else
-            op_sum<T, RB>(I.op, d, it, [&](uint32_t o) { return at(x0, o); }, acc);
+            op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) { return at(x0, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -275,29 +329,39 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
 }
 
 // One Runge-Kutta stage S (2..7), uniform over the launch.
-template <typename T, int RB>
+template <typename T, int RB, int M0>
 __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C, int blk, int S)
 {
     using V = typename vec2<T>::type;
     __shared__ double scr[16];
     __shared__ OpMirror<V, RB> tk, tx;
-    const int d = I.d;
+    int d = I.d;
+    const OpTabs O(I.op);
+    V *Y0 = (V *)I.Y[0], *Y1 = (V *)I.Y[1], *K0 = (V *)I.K[0], *K1 = (V *)I.K[1], *ys0 = (V *)I.ys[0], *ys1 = (V *)I.ys[1];
+    V *k2 = (V *)I.ks[0], *k3 = (V *)I.ks[1], *k4 = (V *)I.ks[2], *k5 = (V *)I.ks[3], *k6 = (V *)I.ks[4];
+    keep(d), keep(Y0), keep(Y1), keep(K0), keep(K1), keep(ys0), keep(ys1);
+    keep(k2), keep(k3), keep(k4), keep(k5), keep(k6);
+    // the column's first entries do not depend on the control record: in flight beside it
     const OpItem<RB> it(blk, d);
-    if (C->status != ST_RUNNING || C->phase != PH_STEP) return;
-    const double h = C->h_try;
-    const int p = C->parity;
-    const T s = (T)C->scale;
-    const V *__restrict__ y = uniform_ptr((const V *)I.Y[p]);
-    const V *__restrict__ k1 = uniform_ptr((const V *)I.K[p]);
-    const V *__restrict__ ynew = uniform_ptr((const V *)I.Y[1 - p]);
-    const V *__restrict__ xin = uniform_ptr(S == 2 ? k1 : (const V *)(S == 7 ? I.Y[1 - p] : I.ys[S & 1 ? 0 : 1]));
+    OpCols<V, M0> pre;
+    pre.load(O, d, it.j, 0);
+    const double2 dj = gld(O.diag + it.j);
+    int status = uniform(C->status), phase = uniform(C->phase), p = uniform(C->parity);
+    double h = uniform(C->h_try), scale = uniform(C->scale);
+    keep(status), keep(phase), keep(p), keep(h), keep(scale);
+    if ((status != ST_RUNNING) | (phase != PH_STEP)) return;
+    const T s = (T)scale;
+    const V *__restrict__ y = p ? Y1 : Y0;
+    const V *__restrict__ k1 = p ? K1 : K0;
+    const V *__restrict__ ynew = p ? Y0 : Y1;
+    const V *__restrict__ xin = S == 2 ? k1 : S == 7 ? ynew : S & 1 ? ys0 : ys1;
     // where the stage's derivative and the next stage's input go
-    V *__restrict__ kout = uniform_ptr((V *)(S == 7 ? I.K[1 - p] : I.ks[S == 7 ? 0 : S - 2]));
-    V *__restrict__ xout = uniform_ptr((V *)(S == 6 ? I.Y[1 - p] : I.ys[S & 1]));
-    const V *__restrict__ q0 = uniform_ptr((const V *)(S == 7 ? I.ks[4] : I.ks[0]));
-    const V *__restrict__ q1 = uniform_ptr((const V *)I.ks[1]);
-    const V *__restrict__ q2 = uniform_ptr((const V *)I.ks[2]);
-    const V *__restrict__ q3 = uniform_ptr((const V *)I.ks[3]);
+    V *__restrict__ kout = S == 7 ? (p ? K0 : K1) : S == 2 ? k2 : S == 3 ? k3 : S == 4 ? k4 : S == 5 ? k5 : k6;
+    V *__restrict__ xout = S == 6 ? (p ? Y0 : Y1) : S & 1 ? ys1 : ys0;
+    const V *__restrict__ q0 = S == 7 ? k6 : k2;
+    const V *__restrict__ q1 = k3;
+    const V *__restrict__ q2 = k4;
+    const V *__restrict__ q3 = k5;
     double e2 = 0.0, l2 = 0.0;
     if (it.i0 < d) {
         V acc[RB], yr, k1r, kr[4]{}, ynr{};
@@ -305,14 +369,15 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
             const uint32_t row = (uint32_t)(it.i[r] * d + it.j) * (uint32_t)sizeof(V);
             yr = at(y, row);
             k1r = at(k1, row);
-            if ((S >= 3 && S <= 5) || S == 7) kr[0] = at(q0, row);
-            if (S >= 4) kr[1] = at(q1, row);
-            if (S >= 5) kr[2] = at(q2, row);
-            if (S >= 6) kr[3] = at(q3, row);
-            if (S == 7) ynr = at(ynew, row);
+            // one row: all of them at once, also what this stage does not use (no branch, no wait)
+            if (RB == 1 || (S >= 3 && S <= 5) || S == 7) kr[0] = at(q0, row);
+            if (RB == 1 || S >= 4) kr[1] = at(q1, row);
+            if (RB == 1 || S >= 5) kr[2] = at(q2, row);
+            if (RB == 1 || S >= 6) kr[3] = at(q3, row);
+            if (RB == 1 || S == 7) ynr = at(ynew, row);
         };
         if constexpr (RB == 1) operands(0);
-        op_sum<T, RB>(I.op, d, it, [&](uint32_t o) { return at(xin, o); }, acc);
+        op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) { return at(xin, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -385,71 +450,86 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
     }
 }
 
-// what: 0 / 1 the starting-step evaluations, 2..7 a stage.  ONE: one problem, descriptor by value, blocks in
-// XCD-contiguous order (a row's sources are then mostly rows of the same XCD's L2); otherwise the block
-// table (bi: problem, br: its block).
-template <typename T, int RB, bool ONE, bool INIT>
+// The stage or starting step `what` of one workgroup: the row count by the dimension, the entries requested
+// at once by the table width (small problems).
+template <typename T, bool INIT, bool SMALL>
+__device__ __forceinline__ void op_body(const CsrInst &I, const CsrCtl *C, int blk, int what)
+{
+    if constexpr (SMALL) {
+        if (I.op.w >= 8) {
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 8>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 8>(I, C, blk, what);
+        } else {
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 4>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 4>(I, C, blk, what);
+        }
+    } else {
+        if constexpr (INIT) op_init_body<T, OP_ROWS, 4>(I, C, blk, what);
+        else op_stage_body<T, OP_ROWS, 4>(I, C, blk, what);
+    }
+}
+
+// Block index in XCD-contiguous order (as csr_block, with the grid as an argument: one line less to read).
+__device__ __forceinline__ int op_block(int n)
+{
+    const int b = blockIdx.x, q = n >> 3, r = n & 7, x = b & 7;
+    return n ? x * q + min(x, r) + (b >> 3) : b;
+}
+
+// what: 0 / 1 the starting-step evaluations, 2..7 a stage.  ONE: one problem, descriptor by value (SMALL: of up
+// to OP_SMALL_D); otherwise the block table (bi: problem, br: its block).  n: the grid, for the XCD-contiguous
+// order (a row's sources are then mostly rows of the same XCD's L2), 0: the launch order.
+template <typename T, bool SMALL, bool ONE, bool INIT>
 __global__ __launch_bounds__(CSR_THREADS) void k_op(const CsrInst *__restrict__ insts, const CsrInst one,
                                                     const CsrCtl *__restrict__ ctls, const int32_t *__restrict__ bi,
-                                                    const int32_t *__restrict__ br, int xcd,
+                                                    const int32_t *__restrict__ br, int n,
                                                     const int32_t *__restrict__ bound, int what)
 {
-    const int lb = csr_block(xcd);
+    const int lb = op_block(n);
     if constexpr (ONE) {
-        if constexpr (INIT) op_init_body<T, RB>(one, ctls, lb, what);
-        else op_stage_body<T, RB>(one, ctls, lb, what);
+        op_body<T, INIT, SMALL>(one, ctls, lb, what);
     } else {
         if (bound && lb >= bound[0]) return;
         const int ii = bi[lb], blk = br[lb];
-        const CsrInst &I = insts[ii];
-        // one launch serves both row counts: the dimension decides
-        if (I.d > OP_SMALL_D) {
-            if constexpr (INIT) op_init_body<T, OP_ROWS>(I, ctls + ii, blk, what);
-            else op_stage_body<T, OP_ROWS>(I, ctls + ii, blk, what);
-        } else {
-            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL>(I, ctls + ii, blk, what);
-            else op_stage_body<T, OP_ROWS_SMALL>(I, ctls + ii, blk, what);
-        }
+        if (insts[ii].d <= OP_SMALL_D) op_body<T, INIT, true>(insts[ii], ctls + ii, blk, what);
+        else op_body<T, INIT, false>(insts[ii], ctls + ii, blk, what);
     }
 }
 
 // Stage 2 with the previous step's control folded in, as k_csr_stage2_ctl.
-template <typename T, int RB>
+template <typename T, bool SMALL>
 __global__ __launch_bounds__(CSR_THREADS) void k_op_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
-                                                               CsrCtl *__restrict__ wr, int xcd)
+                                                               CsrCtl *__restrict__ wr, int n)
 {
     using V = typename vec2<T>::type;
     __shared__ CsrCtl nsh;
     if (!ctl_fold<V, false>(one, rd, wr, nsh, nullptr)) return;
-    op_stage_body<T, RB>(one, &nsh, csr_block(xcd), 2);
+    op_body<T, false, SMALL>(one, &nsh, op_block(n), 2);
 }
 
-template <typename T, int RB> static void op_launch_t(const CsrArgs &a, int what)
+template <typename T, bool SMALL, bool ONE> static void op_launch_t(const CsrArgs &a, int what)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
-#define QT_ARGS a.insts, a.one, a.ctls, a.bi, a.br, a.xcd, a.bound, what
-    if (a.use_one) {
-        if (what < 2) hipLaunchKernelGGL((k_op<T, RB, true, true>), g, t, 0, a.s, QT_ARGS);
-        else hipLaunchKernelGGL((k_op<T, RB, true, false>), g, t, 0, a.s, QT_ARGS);
-    } else {
-        if (what < 2) hipLaunchKernelGGL((k_op<T, OP_ROWS, false, true>), g, t, 0, a.s, QT_ARGS);
-        else hipLaunchKernelGGL((k_op<T, OP_ROWS, false, false>), g, t, 0, a.s, QT_ARGS);
-    }
+    const int n = a.xcd ? a.nblk : 0;
+#define QT_ARGS a.insts, a.one, a.ctls, a.bi, a.br, n, a.bound, what
+    if (what < 2) hipLaunchKernelGGL((k_op<T, SMALL, ONE, true>), g, t, 0, a.s, QT_ARGS);
+    else hipLaunchKernelGGL((k_op<T, SMALL, ONE, false>), g, t, 0, a.s, QT_ARGS);
 #undef QT_ARGS
 }
 
 template <typename T> static void op_launch(const CsrArgs &a, int what)
 {
-    if (a.use_one && a.one.d <= OP_SMALL_D) op_launch_t<T, OP_ROWS_SMALL>(a, what);
-    else op_launch_t<T, OP_ROWS>(a, what);
+    if (!a.use_one) op_launch_t<T, false, false>(a, what);
+    else if (a.one.d <= OP_SMALL_D) op_launch_t<T, true, true>(a, what);
+    else op_launch_t<T, false, true>(a, what);
 }
 
 template <typename T> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
-    if (a.one.d <= OP_SMALL_D)
-        hipLaunchKernelGGL((k_op_stage2_ctl<T, OP_ROWS_SMALL>), g, t, 0, a.s, a.one, rd, wr, a.xcd);
-    else hipLaunchKernelGGL((k_op_stage2_ctl<T, OP_ROWS>), g, t, 0, a.s, a.one, rd, wr, a.xcd);
+    const int n = a.xcd ? a.nblk : 0;
+    if (a.one.d <= OP_SMALL_D) hipLaunchKernelGGL((k_op_stage2_ctl<T, true>), g, t, 0, a.s, a.one, rd, wr, n);
+    else hipLaunchKernelGGL((k_op_stage2_ctl<T, false>), g, t, 0, a.s, a.one, rd, wr, n);
 }
 
 void op_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last)

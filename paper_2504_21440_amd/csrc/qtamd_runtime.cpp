@@ -523,7 +523,7 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
             if (c.ptr[i + 1] - c.ptr[i] > 1) return QT_OK;
     }
     if (w > OP_MAX_W) return QT_OK;
-    w = (w + 1) & ~1;
+    w = std::max(4, (w + 1) & ~1);
     const size_t es = prec == QT_F64 ? 16 : 8, rec = (size_t)w * (8 + 2 * es);
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     const size_t o_lc = up((size_t)d * 16), o_av = o_lc + up((size_t)w * d * 4), o_cv = o_av + up((size_t)w * d * es),
