@@ -333,13 +333,26 @@ static qt_status layout_lanes(qt_me_plan *P)
     return QT_OK;
 }
 
+// Stream j of the lanes beside the first one, made on first use.
+static qt_status lane_stream(qt_me_plan *P, size_t j, hipStream_t *out)
+{
+    while (P->lane_streams.size() <= j) {
+        hipStream_t ns;
+        QT_HIP(hipStreamCreateWithFlags(&ns, hipStreamNonBlocking));
+        P->lane_streams.push_back(ns);
+    }
+    if (out) *out = P->lane_streams[j];
+    return QT_OK;
+}
+
 // One lane with every CSR problem, on the context's stream, control launch over all problems.
 static qt_status reset_lanes(qt_me_plan *P)
 {
     for (auto &l : P->lanes) drop_graph(l);
     P->lanes.assign(1, qt_me_plan::Lane{});
     // resident problems have no launches of their own in a run, and problems with operator tables have a
-    // lane of their own; the stage timing takes every problem through the matrix kernels
+    // lane of their own, on a stream of its own beside the matrix kernels' (16 chains of L = 5 to 8: 10.3 ms, one
+    // lane after the other 12.7); the stage timing takes every problem through the matrix kernels
     qt_me_plan::Lane ops;
     ops.op = true;
     for (auto &m : P->probs) {
@@ -351,10 +364,13 @@ static qt_status reset_lanes(qt_me_plan *P)
         if (P->lanes[0].members.empty()) P->lanes[0] = ops;
         else P->lanes.push_back(ops);
     }
-    for (auto &l : P->lanes) {
+    for (size_t k = 0; k < P->lanes.size(); ++k) {
+        auto &l = P->lanes[k];
         l.listed = (int32_t)l.members.size() < P->ncsr;
         l.done = l.members.empty();
         l.stream = P->ctx->stream;
+        qt_status st;
+        if (k > 0 && (st = lane_stream(P, k - 1, &l.stream))) return st;
     }
     P->split = false;
     return layout_lanes(P);
@@ -773,6 +789,12 @@ qt_status me_plan_run(qt_me_plan *P)
             csr_launch_init(1, L, s);
             QT_HIP(hipGetLastError());
             if ((st = capture_graph(P, (int)k))) return st;
+            auto &l = P->lanes[k];
+            if (l.stream != s) {  // its replays follow the reset and the starting steps
+                if (!l.e1) QT_HIP(hipEventCreate(&l.e1));
+                QT_HIP(hipEventRecord(l.e1, s));
+                QT_HIP(hipStreamWaitEvent(l.stream, l.e1, 0));
+            }
         }
         int64_t last_steps = -1;
         std::vector<double> rem(P->ncsr, 0.0);  // steps still needed, from the current step size
@@ -836,12 +858,8 @@ qt_status me_plan_run(qt_me_plan *P)
                     std::vector<int32_t> slow, rest;
                     for (int32_t i : live) (rem[i] >= 4.0 * med ? slow : rest).push_back(i);
                     if (!slow.empty() && !rest.empty() && (int)P->lanes.size() < 1 + max_extra_lanes()) {
-                        const size_t j = P->lanes.size() - 1;  // streams already made
-                        if (j >= P->lane_streams.size()) {
-                            hipStream_t ns;
-                            QT_HIP(hipStreamCreateWithFlags(&ns, hipStreamNonBlocking));
-                            P->lane_streams.push_back(ns);
-                        }
+                        const size_t j = P->lanes.size() - 1;  // lane k > 0 runs on stream k - 1
+                        if ((st = lane_stream(P, j, nullptr))) return st;
                         qt_me_plan::Lane nlane;
                         nlane.members = slow;
                         nlane.listed = true;

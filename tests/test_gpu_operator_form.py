@@ -132,3 +132,32 @@ def test_widths_and_sizes_in_one_launch(ctx, prec):
     for i, ref in enumerate(lone):
         np.testing.assert_array_equal(got[i], ref)
     srv.close()
+
+
+@pytest.mark.parametrize("prec", [qt.F64, qt.MIXED])
+def test_lanes_shrink_as_problems_finish(ctx, prec):
+    """Operator-form and matrix problems in one plan run in two lanes on two streams; each drops its finished
+    members by itself (six early, two late, one last): bitwise the lone solves, twice."""
+    print(f"[gpu] operator form lanes prec={prec}", flush=True)
+    o = qt.opts(precision=prec, reltol=1e-4)
+    probs, keep = [], []
+    for d, w, nc in [(130, 2, 1), (72, 14, 2)]:
+        for t in [0.1, 0.1, 0.1, 0.1, 0.1, 0.1, 4.0, 4.0, 40.0]:
+            H, cs, psi, e = _model(d, w, nc, d + w)
+            keep.append(qt.Liouvillian(ctx, H, cs, qt.FORM_CSR, prec))
+            probs.append((keep[-1], psi, np.linspace(0.0, t, 3), e))
+    lone = {}
+    plan = qt.MePlan(ctx, probs, o)
+    plan.set_shape(8, 1, 0, 2)
+    for _ in range(2):
+        plan.run()
+        for i, p in enumerate(probs):
+            key = (i // 9, p[2][-1])
+            if key not in lone:
+                q = qt.MePlan(ctx, [p], o)
+                q.set_shape(8, 1, 0, 2)
+                q.run()
+                lone[key] = q.result(0)[0]
+                q.close()
+            np.testing.assert_array_equal(plan.result(i)[0], lone[key])
+    plan.close()
