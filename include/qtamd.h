@@ -172,7 +172,9 @@ qt_status qt_liouv_terms(const qt_liouv *L, int32_t *n_terms);
 qt_status qt_liouv_info(const qt_liouv *L, int32_t *d, int64_t *nnz, int64_t *bytes);
 /* Device bytes the Liouvillian holds until qt_liouv_destroy: CSR row pointers, columns and values
  * (and the coefficient tables of a time-dependent one), or the dense operators.  A served request
- * is charged this plus its own state (qt_server_footprint). */
+ * is charged this plus its own state (qt_server_footprint).  A constant CSR Liouvillian whose
+ * operators have few entries per row keeps them beside it (at most 12 entries per row of each of two
+ * d x d tables, twice), which is not counted. */
 qt_status qt_liouv_footprint(const qt_liouv *L, size_t *bytes);
 /* Copies the assembled CSR back to the host (values widened to complex128, row padding left out).
  * indptr: d*d + 1, indices and values: nnz from qt_liouv_info.  CSR form only. */
@@ -246,7 +248,8 @@ qt_status qt_steadystate(qt_ctx *ctx, const qt_liouv *L, const double *rho0, int
 /* Measurement: average device duration (HIP events on the plan's stream) of one right-hand-side
  * launch over `reps` back-to-back launches.  CSR problems: one fused SpMV-stage kernel (the stage
  * that forms the fourth stage input) over every CSR problem of the plan, from a freshly reset
- * state.  Plans with only dense problems: one whole-solve launch of the dense kernels.  The plan's
+ * state, also where a run would take another solver (one workgroup per small problem, or the
+ * operator form).  Plans with only dense problems: one whole-solve launch of the dense kernels.  The plan's
  * results are unspecified afterwards until the next qt_me_plan_run. */
 qt_status qt_me_plan_time_rhs(qt_me_plan *plan, int32_t reps, double *ms_per_launch);
 
@@ -285,6 +288,12 @@ qt_status qt_measure_read_bandwidth(qt_ctx *ctx, int64_t bytes, int32_t reps, do
  * which every later plan consults.  The plan's results are unspecified afterwards until the next
  * qt_me_plan_run.  qt_me_plan_shape reports the shape in use (zeros for a group the plan does not
  * have); qt_me_plan_set_shape imposes a CSR shape (QT_EINVAL if the kernels do not support it).
+ * The shape is that of the kernels that read the assembled matrix.  A run of a constant problem whose
+ * initial state is exactly Hermitian takes them only if it is neither small (d up to 80, or 62 in FP64,
+ * with at most 16 entries per row of L: one workgroup integrates it) nor large with sparse operators
+ * (d > 128, at most 12 off-diagonal entries per row of H - i/2 sum C^dag C, at most 12 C_k of one entry per
+ * row: the operators are applied themselves).  Which solver a problem takes depends on the problem
+ * alone.
  * One shape serves every CSR problem of a plan; the row-sum and norm reduction orders follow
  * lanes_per_row and rows_per_group only, so a problem's results are bitwise the same alone and in
  * a batch, and with either xcd_order or cached_matrix, when those two are the same.  The dense

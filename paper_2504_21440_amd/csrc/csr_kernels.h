@@ -712,17 +712,17 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_stage(const CsrInst *__rest
 // launch swaps them.  rd->pending is 0 right after the starting step (no stage 7 to decide yet).
 // Removes the control launch from every step.
 //
-// ctl_fold: the decision, into nsh (shared) and, from workgroup 0, into wr; false for a finished problem.
-// cw2 (shared, time-dependent problems): stage 2's coefficient row when a step was decided.
+// ctl_fold: the decision, into nsh (shared) and, from workgroup 0, into wr; 0 for a finished problem, else 1,
+// or 2 when a step of a time-dependent problem was decided: stage 2's coefficient row is then in cw2 (shared).
 template <typename V, bool TD>
-__device__ __forceinline__ bool ctl_fold(const CsrInst &I, const CsrCtl *__restrict__ rd, CsrCtl *__restrict__ wr,
+__device__ __forceinline__ int ctl_fold(const CsrInst &I, const CsrCtl *__restrict__ rd, CsrCtl *__restrict__ wr,
                                          CsrCtl &nsh, V *cw2)
 {
     __shared__ double scr[32];
     const CsrCtl c = *rd;
     if (c.status != ST_RUNNING || c.phase != PH_STEP) {  // finished: carry the record forward
         if (blockIdx.x == 0 && threadIdx.x == 0) *wr = c;
-        return false;
+        return 0;
     }
     if (c.pending) {
         const int sidx = c.save_idx;
@@ -753,9 +753,10 @@ __device__ __forceinline__ bool ctl_fold(const CsrInst &I, const CsrCtl *__restr
                 cw2[threadIdx.x] = from_d2<V>(w2);
             }
             __syncthreads();
+            return 2;
         }
     }
-    return true;
+    return 1;
 }
 
 template <typename T, int LPR, int RG, bool TD>
@@ -765,10 +766,11 @@ __global__ __launch_bounds__(CSR_THREADS) void k_csr_stage2_ctl(const CsrInst on
     using V = typename vec2<T>::type;
     __shared__ CsrCtl nsh;
     __shared__ V cw2[TD ? TD_MAX_TERMS + 1 : 1];
-    if (!ctl_fold<V, TD>(one, rd, wr, nsh, cw2)) return;
+    const int go = ctl_fold<V, TD>(one, rd, wr, nsh, cw2);
+    if (!go) return;
     const V *cw = nullptr;  // stage 2's coefficient row (time-dependent problems)
     if constexpr (TD)
-        if (rd->pending && nsh.status == ST_RUNNING && one.nterms > 0) cw = cw2;
+        if (go == 2) cw = cw2;
     stage_body<T, LPR, RG, 2, true, true, TD>(one, &nsh, blockIdx.x * CsrGeom<LPR, RG>::RPB, blockIdx.x, cw);
 }
 

@@ -127,16 +127,23 @@ __device__ __forceinline__ double uniform(double v)
 // first use, one round trip to memory after the other.
 template <typename P> __device__ __forceinline__ void keep(P &p) { asm volatile("" : "+s"(p)); }
 
-// A problem's tables, read from its descriptor at once.
+// A problem's tables (es: bytes of a state element), their descriptor read at once.
 struct OpTabs {
     int w;
     const double2 *diag;
     const int32_t *lcol;
     const void *aval, *cval, *rows;
-    __device__ __forceinline__ explicit OpTabs(const OpForm &O)
-        : w(O.w), diag(O.diag), lcol(O.lcol), aval(O.aval), cval(O.cval), rows(O.rows)
+    __device__ __forceinline__ OpTabs(const OpForm &O, int d, uint32_t es)
     {
-        keep(w), keep(diag), keep(lcol), keep(aval), keep(cval), keep(rows);
+        const char *mem = (const char *)O.mem;
+        w = O.w;
+        keep(w), keep(mem);
+        const OpOffsets o(d, w, es);
+        diag = (const double2 *)mem;
+        lcol = (const int32_t *)(mem + o.lcol);
+        aval = mem + o.aval;
+        cval = mem + o.cval;
+        rows = mem + o.rows;
     }
 };
 
@@ -274,7 +281,7 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
     V *__restrict__ y = uniform_ptr((V *)I.Y[0]);
     V *__restrict__ k1 = uniform_ptr((V *)I.K[0]);
     double sa = 0.0, sb = 0.0;
-    const OpTabs O(I.op);
+    const OpTabs O(I.op, d, sizeof(V));
     if (it.i0 < d) {
         OpCols<V, M0> pre;
         pre.load(O, d, it.j, 0);
@@ -336,11 +343,11 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
     __shared__ double scr[16];
     __shared__ OpMirror<V, RB> tk, tx;
     int d = I.d;
-    const OpTabs O(I.op);
     V *Y0 = (V *)I.Y[0], *Y1 = (V *)I.Y[1], *K0 = (V *)I.K[0], *K1 = (V *)I.K[1], *ys0 = (V *)I.ys[0], *ys1 = (V *)I.ys[1];
     V *k2 = (V *)I.ks[0], *k3 = (V *)I.ks[1], *k4 = (V *)I.ks[2], *k5 = (V *)I.ks[3], *k6 = (V *)I.ks[4];
     keep(d), keep(Y0), keep(Y1), keep(K0), keep(K1), keep(ys0), keep(ys1);
     keep(k2), keep(k3), keep(k4), keep(k5), keep(k6);
+    const OpTabs O(I.op, d, sizeof(V));
     // the column's first entries do not depend on the control record: in flight beside it
     const OpItem<RB> it(blk, d);
     OpCols<V, M0> pre;

@@ -97,7 +97,6 @@ struct Liouv {
     // operator tables of the staged solver (kernels_op.hip; device pointers into op_mem, op.w = 0: none)
     OpForm op{};
     void *op_mem = nullptr;
-    int64_t op_bytes = 0;
     // resident solver (kernels_res.hip): the most generator entries of an element (0: not eligible) and,
     // in the dense form, the upper-triangle ELL a plan or server uploads (res_build_ell)
     int32_t res_w = 0;

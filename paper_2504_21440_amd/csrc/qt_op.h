@@ -17,13 +17,30 @@ constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
 // itself with value 0 (jumps: column -1).  Kernels index a problem's tables with its own w, never with
 // another's of the same launch.  Every table exists twice, entry by entry over the columns (what 64 lanes
 // read) and row by row (what a wave reads for its rows).
+//   diag [d]     A_ii
+//   lcol [w][d]  column of A's off-diagonal entry | column of C_c's entry << 16 (0xffff: none)
+//   aval [w][d]  A's values, state precision
+//   cval [w][d]  C_c's value, state precision
+//   rows [d]     records: columns of A [w], of the jumps [w] (-1: none), values of A [w], of the jumps [w]
+// One allocation holds them, so that descriptors (kernel arguments of every CSR launch) stay short.
 struct OpForm {
+    const void *mem;
     int32_t w, pad;
-    const double2 *diag;   // [d] A_ii
-    const int32_t *lcol;   // [w][d] column of A's off-diagonal entry | column of C_c's entry << 16 (0xffff: none)
-    const void *aval;      // [w][d] A's values, state precision
-    const void *cval;      // [w][d] C_c's value, state precision
-    const void *rows;      // [d] records: columns of A [w], of the jumps [w] (-1: none), values of A [w], of the jumps [w]
+};
+
+// Byte offsets of the tables (diag at 0) for state elements of es bytes, and the bytes of all.
+struct OpOffsets {
+    uint32_t lcol, aval, cval, rows, total;
+    __host__ __device__ OpOffsets(int d, int w, uint32_t es)
+    {
+        const uint32_t n = (uint32_t)w * (uint32_t)d;
+        lcol = up((uint32_t)d * 16u);
+        aval = lcol + up(n * 4u);
+        cval = aval + up(n * es);
+        rows = cval + up(n * es);
+        total = rows + up(n * (8u + 2u * es));
+    }
+    static __host__ __device__ uint32_t up(uint32_t b) { return (b + 255u) & ~255u; }
 };
 
 // Rows one wave serves: fixed by the dimension, so that a problem's sums do not depend on the plan.  Up to

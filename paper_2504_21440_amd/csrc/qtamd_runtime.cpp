@@ -525,9 +525,8 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
     if (w > OP_MAX_W) return QT_OK;
     w = std::max(4, (w + 1) & ~1);
     const size_t es = prec == QT_F64 ? 16 : 8, rec = (size_t)w * (8 + 2 * es);
-    auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t o_lc = up((size_t)d * 16), o_av = o_lc + up((size_t)w * d * 4), o_cv = o_av + up((size_t)w * d * es),
-                 o_rec = o_cv + up((size_t)w * d * es), total = o_rec + up((size_t)d * rec);
+    const OpOffsets o(d, w, (uint32_t)es);
+    const size_t o_lc = o.lcol, o_av = o.aval, o_cv = o.cval, o_rec = o.rows, total = o.total;
     std::vector<char> h(total, 0);
     double2 *diag = (double2 *)h.data();
     int32_t *lc = (int32_t *)(h.data() + o_lc);
@@ -560,17 +559,15 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
             put(rcv, c, cs[c].val[cs[c].ptr[i]]);
         }
     }
-    if (hipMalloc(&L->op_mem, total) != hipSuccess) return set_error(QT_ENOMEM, "hipMalloc operator tables");
+    if (hipMalloc(&L->op_mem, total) != hipSuccess) {  // then the matrix kernels take the problem
+        (void)hipGetLastError();
+        L->op_mem = nullptr;
+        return QT_OK;
+    }
     if (hipMemcpy(L->op_mem, h.data(), total, hipMemcpyHostToDevice) != hipSuccess)
         return set_error(QT_EDEVICE, "upload operator tables");
-    L->op_bytes = (int64_t)total;
-    const char *b = (const char *)L->op_mem;
+    L->op.mem = L->op_mem;
     L->op.w = w;
-    L->op.diag = (const double2 *)b;
-    L->op.lcol = (const int32_t *)(b + o_lc);
-    L->op.aval = b + o_av;
-    L->op.cval = b + o_cv;
-    L->op.rows = b + o_rec;
     return QT_OK;
 }
 
@@ -867,14 +864,14 @@ qt_status qt_liouv_info(const qt_liouv *L, int32_t *d, int64_t *nnz, int64_t *by
     if (!L) return set_error(QT_EINVAL, "null Liouvillian");
     if (d) *d = L->d;
     if (nnz) *nnz = L->nnz;
-    if (bytes) *bytes = L->bytes + L->op_bytes;
+    if (bytes) *bytes = L->bytes;
     return QT_OK;
 }
 
 qt_status qt_liouv_footprint(const qt_liouv *L, size_t *bytes)
 {
     if (!L || !bytes) return set_error(QT_EINVAL, "qt_liouv_footprint: null argument");
-    *bytes = (size_t)(L->bytes + L->op_bytes);
+    *bytes = (size_t)L->bytes;
     return QT_OK;
 }
 
