@@ -3,14 +3,15 @@
 Headline workload (one "step" = one full adaptive solve): the dissipative transverse-field Ising
 chain, L = 8 (d = 256, Liouvillian 65,536 x 65,536 with 1,245,183 non-zeros), J = 1, h = 0.7,
 gamma = 0.2, all spins up, t in [0, 10], <sigma_z^i> at 100 times, solved by the mixed-precision
-CSR path (complex64 SpMV and stages, FP64 step control / error norm / trace / expectations) at the
+CSR path (complex64 right-hand side and stages, FP64 step control / error norm / trace / expectations) at the
 loosest tolerance whose result stays within 1e-4 of a tight FP64 oracle solution.
 ``value`` = Liouvillian right-hand-side evaluations per second over the timed solves.
 
-The same JSON line carries: the FP64 single-solve path on the same problem, the roofline of the
-fused SpMV-stage kernel (live, HIP events) at this size and at an HBM-sized Liouvillian (L = 10)
-beside the measured copy and read bandwidth, the 512-cavity parameter sweep (batched solves/s: all
-on the matrix cores, with TFLOP/s, and with the costliest cavities routed to the CSR form), the
+The same JSON line carries: the FP64 single-solve path on the same problem, the rate of the solve's
+right-hand side against the vector peak, the roofline of the fused SpMV-stage kernel (live, HIP
+events; what a solve takes whose operators have no operator form) at this size and at an HBM-sized
+Liouvillian (L = 10) beside the measured copy and read bandwidth, the 512-cavity parameter sweep (batched solves/s: all
+in the dense form, and with the costliest cavities in the CSR form), the
 quantum-jump ensemble (trajectories/s), the served request stream (p50/p99 latency over a load
 sweep), the time-dependent, stochastic, Schrodinger and steady-state solvers, and the FP64 CPU
 oracle timed on this host.
@@ -33,7 +34,6 @@ import workloads  # noqa: E402
 import paper_2504_21440_amd as qt  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
-FP32_MATRIX_PEAK_TFLOPS = 157.3
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 METRIC = "Lindblad RHS evals/s + batched solves/s at 1e-4 error vs FP64; p50/p99 latency"
 LADDER = [1e-4, 3e-5, 1e-5, 3e-6, 1e-6]
@@ -163,7 +163,7 @@ def section_ising_batch(ctx, rt, steps, warmup, n=16):
 def section_kerr_single(ctx, reps=5):
     """The driven Kerr cavity (N = 20, Delta = 1, U = 0.5, F = 0.8, kappa = 1) in plain FP64 at the
     default tolerances (abstol 1e-8, reltol 1e-6), t in [0, 20] with <a^dag a> at 200 times, CSR form
-    (400 Liouville rows, 2,280 non-zeros: 60 KB per SpMV, so every launch is latency-bound): RHS
+    (400 Liouville rows, 2,280 non-zeros; one workgroup integrates it): RHS
     evaluations per second, solve time and steps, the error against the stored FP64 oracle solution
     (same integrator and tolerances), and the U = 0 variant against the coherent-state closed form
     alpha(t) = alpha_ss (1 - exp(-(i Delta + kappa/2) t)), alpha_ss = -i F / (i Delta + kappa/2)."""
@@ -268,7 +268,7 @@ def sweep_forms(sweep, policy):
 
 def section_sweep(ctx, n=512, policy="dense"):
     """512 driven Kerr cavities, N ~ U{10..80}, mixed precision, one plan.  The policy (sweep_forms)
-    picks each cavity's form; CSR-form launches run concurrently with the dense buckets."""
+    picks each cavity's form; one workgroup integrates a cavity of either form."""
     sweep = workloads.kerr_sweep(n=n)
     forms = sweep_forms(sweep, policy)
     probs = []
@@ -281,10 +281,8 @@ def section_sweep(ctx, n=512, policy="dense"):
         rho0[0, 0] = 1
         num = np.diag(np.arange(p["N"], dtype=float)).astype(complex)
         probs.append((Lo, rho0, workloads.tlist(p["t_end"], p["nt"]), [num]))
-    # untimed set-up: the autotuner picks the waves per workgroup for each padded size
     o = qt.opts(abstol=1e-7, reltol=1e-5, precision=qt.MIXED, autotune=True)
     plan = qt.MePlan(ctx, probs, o)
-    waves = plan.shape()[4]
     plan.run()
     t0 = time.perf_counter()
     plan.run()
@@ -297,7 +295,7 @@ def section_sweep(ctx, n=512, policy="dense"):
         ex, st, _ = plan.result(i)
         res.append(ex)
         n_rhs += st["n_rhs"]
-        flops += st["n_rhs"] * 24.0 * p["N"] ** 3
+        flops += st["n_rhs"] * 24.0 * p["N"] * (p["N"] + 1)
         worst = max(worst, (st["n_rhs"], i))
     with open(os.path.join(ROOT, "tests", "golden", "kerr_sweep_samples.json")) as f:
         samples = json.load(f)["instances"]
@@ -308,23 +306,12 @@ def section_sweep(ctx, n=512, policy="dense"):
            "csr_instances": sum(1 for f in forms if f == qt.FORM_CSR),
            "max_err_vs_fp64_oracle_samples": err, "samples_checked": [q["index"] for q in samples]}
     if policy == "dense":
-        # the concurrent run: all 512 dense instances in flight together, flops at the true N
-        # (24 N^3 per right-hand side: the 1 + 2K complex products of the operator form, K = 1)
-        out.update({"algorithmic_TFLOPs_concurrent": flops / dt / 1e12,
-                    "frac_of_fp32_matrix_peak_concurrent": flops / dt / 1e12 / FP32_MATRIX_PEAK_TFLOPS,
-                    "dense_waves_largest_bucket": waves})
-        # The stiffest cavity sets the makespan.  MFMA instructions per right-hand side at padded
-        # size NP (real collapse operator): P and X on every 16x16 tile (4 + 2 per inner step),
-        # C X^dag on the upper tiles (2), NP / 4 inner steps; 32 cycles each on one of 4 SIMDs.
+        # One workgroup integrates one cavity (k_res): 6 generator entries per element, one complex FMA each,
+        # on the elements i <= j.  The stiffest cavity sets the makespan.
         nw, iw = worst
-        npad = -(-sweep[iw]["N"] // 16) * 16
-        nt, kf = npad // 16, npad // 4
-        mfma = nt * nt * kf * 6 + nt * (nt + 1) // 2 * kf * 2
-        us = dt / nw * 1e6
-        mfma_us = mfma * 32 / 4 / 2.4e3
-        out["stiffest_instance"] = {"index": iw, "N": sweep[iw]["N"], "n_rhs": nw, "us_per_rhs": us,
-                                    "mfma_instructions_per_rhs": mfma, "mfma_us_per_rhs_at_2400MHz": mfma_us,
-                                    "mfma_busy_share_of_its_cu": mfma_us / us}
+        out["algorithmic_TFLOPs_concurrent"] = flops / dt / 1e12
+        out["frac_of_fp32_vector_peak_concurrent"] = flops / dt / 1e12 / FP32_VECTOR_PEAK_TFLOPS
+        out["stiffest_instance"] = {"index": iw, "N": sweep[iw]["N"], "n_rhs": nw, "us_per_rhs": dt / nw * 1e6}
     else:
         out["csr_shape"] = list(plan.shape()[:4])
     plan.close()
@@ -343,7 +330,6 @@ def section_mc(ctx):
     d = Heff.shape[0]
     width = int(np.diff(Heff.indptr).max())  # ELL width of -i H_eff (entries per row)
     flops_rhs = 8.0 * d * width              # one complex FMA per stored entry
-    l2_bytes_rhs = d * width * (8 + 4)       # complex64 value + int32 column per entry, read from L2
     out = {"ntraj": p["ntraj"], "d": d, "ell_width": width}
     for name, prec in [("mixed", qt.MIXED), ("fp64", qt.F64)]:
         o = qt.opts(abstol=1e-6, reltol=1e-4, precision=prec)
@@ -361,11 +347,10 @@ def section_mc(ctx):
                "points_over_3se": int((z > 3).sum()), "rtol": o.reltol, "atol": o.abstol}
         if prec == qt.MIXED:
             tf = st["n_rhs"] * flops_rhs / (st["device_ms"] * 1e-3) / 1e12
-            sec["roofline"] = {"kernel": "k_mc<float,4,false,3> (one workgroup per trajectory, state in registers)",
+            sec["roofline"] = {"kernel": "k_mc<float,...> (one workgroup per trajectory; state and -i H_eff in registers)",
                                "bound": "alu", "flops_per_traj_rhs": flops_rhs,
-                               "l2_bytes_per_traj_rhs": l2_bytes_rhs, "achieved_TFLOPs": tf,
-                               "peak_TFLOPs": FP32_VECTOR_PEAK_TFLOPS, "frac": tf / FP32_VECTOR_PEAK_TFLOPS,
-                               "l2_read_GBs": st["n_rhs"] * l2_bytes_rhs / (st["device_ms"] * 1e-3) / 1e9}
+                               "achieved_TFLOPs": tf, "peak_TFLOPs": FP32_VECTOR_PEAK_TFLOPS,
+                               "frac": tf / FP32_VECTOR_PEAK_TFLOPS}
         out[name] = sec
         plan.close()
     log(f"mc: {out}")
@@ -1014,12 +999,21 @@ def main():
     # kernel FORM of a single-problem plan: 1 streamed, 2 cached, 4 cached with 16-byte loads
     kname = "k_csr_stage<float,%d,%d,%d,3,false>" % (mixed["csr_shape"][0], mixed["csr_shape"][1],
                                                      (1, 2, 4)[mixed["csr_shape"][3]])
-    rl = {"bound": "hbm", "achieved": mixed["stage_kernel_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-          "frac": mixed["stage_kernel_GBs"] / HBM_PEAK_GBS, "traffic": profiled_traffic(kname),
-          "kernel": kname + " (fused SpMV + stage epilogue), L=8 Liouvillian, one launch = one SpMV",
-          "algorithmic_bytes": mixed["spmv_bytes"],
-          "regime": "the 16 MB matrix stays in the 256 MB MALL between launches, so this launch is bound by "
-                    "latency, not HBM; the HBM evidence is spmv_hbm_L10",
+    matrix = {"bound": "hbm", "achieved": mixed["stage_kernel_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+              "frac": mixed["stage_kernel_GBs"] / HBM_PEAK_GBS, "traffic": profiled_traffic(kname),
+              "kernel": kname + " (fused SpMV + stage epilogue), L=8 Liouvillian, one launch = one SpMV",
+              "algorithmic_bytes": mixed["spmv_bytes"],
+              "regime": "timed alone: the solve applies the operators (k_op) instead; the 16 MB matrix stays in the "
+                        "256 MB MALL between launches, so this launch is bound by latency, not HBM; the HBM "
+                        "evidence is spmv_hbm_L10"}
+    # the solve's own right-hand side: 8 flops per entry of the superoperator it stands for, over the whole solve
+    tf = 8.0 * mixed["nnz"] * mixed["rhs_per_s"] / 1e12
+    rl = {"bound": "latency", "achieved": tf, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
+          "frac": tf / FP32_VECTOR_PEAK_TFLOPS,
+          "kernel": "k_op<float,true,true,false> (operator form, upper triangle), L=8 chain, one launch = one stage",
+          "regime": "us_per_rhs over the whole solve, launches and step control included; a stage is one launch of "
+                    "160 workgroups, bound by the latency of a wave",
+          "us_per_rhs": 1e6 / mixed["rhs_per_s"], "matrix_stage_kernel": matrix,
           "measured_copy_GBs": copy["GBs"], "measured_read_GBs": copy["read_GBs"]}
     line = {
         "metric": METRIC, "value": mixed["rhs_per_s"], "unit": "RHS evals/s", "n_gpus": 1, "steps": args.steps,
