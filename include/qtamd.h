@@ -467,7 +467,7 @@ typedef struct {
 
 qt_status qt_server_create(qt_ctx *ctx, const qt_server_cfg *cfg, qt_server **out);
 /* The server's device memory is one region sized at creation: the request pool (pool_bytes), the
- * slot-indexed descriptors and control records, and the block tables of both lanes at their largest
+ * slot-indexed descriptors and control records, and the block tables of its lanes at their largest
  * admissible size, so submit, step and poll never allocate device memory.  qt_server_workspace
  * reports its bytes; qt_server_create_ws places it in the caller's buffer (256-byte aligned device
  * memory on the context's device, kept until qt_server_destroy) instead of allocating it. */

@@ -13,8 +13,8 @@ constexpr int OP_MAX_W = 12;  // off-diagonal entries per row of A, and collapse
 constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
 
 // L(rho) = A rho + rho A^dag + sum_c C_c rho C_c^dag from d x d tables (device pointers; w = 0: none).
-// w is the problem's table width, even and at least 4: entries past a row's own (and channels past the last) are the row
-// itself with value 0 (jumps: column -1).  Kernels index a problem's tables with its own w, never with
+// w is the problem's table width, even and at least 4: entries past a row's own (and channels past the last)
+// are the row itself with value 0 (jumps: column -1).  Kernels index a problem's tables with its own w, never with
 // another's of the same launch.  Every table exists twice, entry by entry over the columns (what 64 lanes
 // read) and row by row (what a wave reads for its rows).
 //   diag [d]     A_ii

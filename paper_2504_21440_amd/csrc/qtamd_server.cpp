@@ -11,8 +11,9 @@
 // work overlaps on the device with whatever else is resident.  A request's arithmetic does not
 // depend on what else is resident: its blocks, reductions and step decisions are its own.
 //
-// CSR requests run in two lanes, each with its own block table, epoch graphs and stream: large
-// Liouvillians on the context's stream, small ones on its auxiliary stream.  A small problem's
+// CSR requests that are not resident run in four lanes, each with its own block table and epoch graphs:
+// large (0: matrix kernels, 2: operator form) on the context's stream, small ones (1, 3) on its auxiliary
+// stream.  A small problem's
 // step costs a few microseconds of launch latency, a large one's far more, so in one shared table
 // a stiff small request would advance only at the large ones' pace.  While the large lane's epoch
 // runs, the small lane replays its own epoch graph, until the large lane finishes or no small
