@@ -299,6 +299,13 @@ static void drop_graph(qt_me_plan::Lane &l)
     l.graph = nullptr;
 }
 
+static void drop_events(qt_me_plan::Lane &l)
+{
+    if (l.e0) (void)hipEventDestroy(l.e0);
+    if (l.e1) (void)hipEventDestroy(l.e1);
+    l.e0 = l.e1 = nullptr;
+}
+
 // Write the block table and control list of every live lane, back to back, and upload them.  A
 // lane's blocks are those of its members at the plan's shape.  Graphs are recaptured on next use.
 static qt_status layout_lanes(qt_me_plan *P)
@@ -348,7 +355,7 @@ static qt_status lane_stream(qt_me_plan *P, size_t j, hipStream_t *out)
 // One lane with every CSR problem, on the context's stream, control launch over all problems.
 static qt_status reset_lanes(qt_me_plan *P)
 {
-    for (auto &l : P->lanes) drop_graph(l);
+    for (auto &l : P->lanes) drop_graph(l), drop_events(l);
     P->lanes.assign(1, qt_me_plan::Lane{});
     // resident problems have no launches of their own in a run, and problems with operator tables have a
     // lane of their own, on a stream of its own beside the matrix kernels' (16 chains of L = 5 to 8: 10.3 ms, one
@@ -1228,8 +1235,7 @@ qt_status qt_me_plan_destroy(qt_me_plan *P)
     (void)hipSetDevice(P->ctx->device);
     for (auto &l : P->lanes) {
         drop_graph(l);
-        if (l.e0) (void)hipEventDestroy(l.e0);
-        if (l.e1) (void)hipEventDestroy(l.e1);
+        drop_events(l);
     }
     for (hipStream_t ls : P->lane_streams) (void)hipStreamDestroy(ls);
     if (P->h_cctl) (void)hipHostFree(P->h_cctl);
