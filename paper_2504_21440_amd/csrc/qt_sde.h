@@ -20,7 +20,6 @@ constexpr int SDE_MAX_SC = 8;     // measured operators
 
 struct SdeParams {
     int32_t n, d, m, ne, nt, rows, sme;
-    int32_t occ2;          // complex64 variant held to 2 waves per SIMD (set by sde_choose_variant)
     int32_t WA, WB;       // ELL widths of A and of each B_n
     double cg;
     uint64_t seed;
@@ -46,8 +45,6 @@ struct SdeParams {
 // size; null when the problem has none.
 const void *sde_reg_kernel(const SdeParams &p, bool f64, int *threads);
 size_t sde_lds_bytes(const SdeParams &p, bool f64);
-// Sets p.occ2 from the ensemble size and the device's compute-unit count.
-void sde_choose_variant(SdeParams &p, bool f64, int device);
 int sde_grid(const SdeParams &p, bool f64, int device);
 void sde_launch(const SdeParams &p, const SdeParams *dev_p, bool f64, int grid, hipStream_t s);
 

@@ -241,7 +241,6 @@ static qt_status sde_plan_create(Ctx *ctx, const qt_sde_problem *pr, int32_t mas
     p.cg = master ? 1.0 : 0.5;
     p.seed = pr->seed;
     p.ntraj = pr->ntraj;
-    sde_choose_variant(p, f64, ctx->device);
     if (sde_lds_bytes(p, f64) > 160 * 1024) {
         delete P;
         return set_error(QT_EINVAL, "state and measured-operator images exceed the 160 KB of LDS");
