@@ -22,11 +22,12 @@
 // elements; four rows took 40 us (too few waves in flight), one row 33 us.  Sixteen chains of L = 8: 20 us a
 // stage against 45 to 60 us.
 //
-// The diagonal is formed in FP64 and rounded once, as the assembled matrix holds it.  Everything else of a
+// Precision: as in the assembled matrix, the factor of the element itself (the diagonals of A and the jumps that
+// start from the element) is summed in FP64 and rounded once, and so is each product of two C entries.  With
+// products of rounded C entries a diagonal channel's decay and jump, which cancel in the matrix, left 2e-7 of
+// the rate: after t = 100 with C = sqrt(0.1) n (d = 160) populations had drifted by 1e-4.  Everything else of a
 // step -- stage combinations, error partials, control, expectation values -- is that of kernels_csr.hip, on
 // the same descriptors, with op_blocks(d) partials a problem.
-#include <type_traits>
-
 #include "csr_kernels.h"
 
 namespace qt {
@@ -129,27 +130,30 @@ template <typename P> __device__ __forceinline__ void keep(P &p) { asm volatile(
 
 // A problem's tables (es: bytes of a state element), their descriptor read at once.
 struct OpTabs {
-    int w;
+    int w, self;
     const double2 *diag;
     const int32_t *lcol;
-    const void *aval, *cval, *rows;
+    const void *aval, *rows;
+    const double2 *cval;
     __device__ __forceinline__ OpTabs(const OpForm &O, int d, uint32_t es)
     {
         const char *mem = (const char *)O.mem;
         w = O.w;
-        keep(w), keep(mem);
+        self = O.self;
+        keep(w), keep(self), keep(mem);
         const OpOffsets o(d, w, es);
         diag = (const double2 *)mem;
         lcol = (const int32_t *)(mem + o.lcol);
         aval = mem + o.aval;
-        cval = mem + o.cval;
+        cval = (const double2 *)(mem + o.cval);
         rows = mem + o.rows;
     }
 };
 
 // M entries of this lane's column, from entry k on.
 template <typename V, int M> struct OpCols {
-    V a[M], c[M];   // conj A_jl; C_c's value
+    V a[M];         // conj A_jl
+    double2 c[M];   // C_c's value
     uint32_t l[M];  // their columns
     __device__ __forceinline__ void load(const OpTabs &O, int d, int j, int k)
     {
@@ -159,7 +163,7 @@ template <typename V, int M> struct OpCols {
             l[m] = (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u));
             a[m] = at((const V *)O.aval, q * (uint32_t)sizeof(V));
             a[m].y = -a[m].y;
-            c[m] = at((const V *)O.cval, q * (uint32_t)sizeof(V));
+            c[m] = at(O.cval, q * 16u);
         }
     }
 };
@@ -180,19 +184,23 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
     const uint32_t ds = (uint32_t)d * ES, jo = (uint32_t)it.j * ES;
     const int32_t *rac[RB];
     const V *rav[RB];
+    const double2 *rcv[RB];
     V own[RB];
-    double2 di[RB];
+    double2 dd[RB];  // what the element itself is multiplied by
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-        const char *rec = (const char *)O.rows + (uint32_t)(it.i[r] * w) * (uint32_t)(8 + 2 * ES);
+        const char *rec = (const char *)O.rows + (uint32_t)it.i[r] * OpOffsets::rec(w, ES);
         rac[r] = (const int32_t *)rec;              // [w] columns of A, [w] columns of the jumps
-        rav[r] = (const V *)(rec + 8 * (size_t)w);  // [w] values of A, [w] of the jumps
-        di[r] = uld(O.diag + it.i[r]);
+        rav[r] = (const V *)(rec + 8 * (size_t)w);  // [w] values of A
+        rcv[r] = (const double2 *)(rec + (8 + ES) * (size_t)w);  // [w] of the jumps
+        dd[r] = uld(O.diag + it.i[r]);
+        dd[r].x += dj.x;
+        dd[r].y -= dj.y;
         own[r] = x((uint32_t)it.i[r] * ds + jo);
+        acc[r].x = acc[r].y = T(0);
     }
-    auto part = [&](auto first, const auto &col, int k) {
+    auto part = [&](const auto &col, int k) {
         constexpr int M = sizeof(col.l) / 4;
-        constexpr bool FIRST = decltype(first)::value;
         V up[RB][M], side[RB][M], jump[RB][M];
         // A rho: the column's other rows
 #pragma unroll
@@ -205,34 +213,38 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 #pragma unroll
                 for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (col.l[m] & 0xffffu) * ES);
         };
-        auto load_jump = [&]() {  // the jumps; an element without one takes itself, times zero
+        // the jumps; an element without one takes itself, times zero, as does one whose jump starts from the element
+        // (counted in dd)
+        V v[RB][M];
+        auto load_jump = [&]() {
+            uint32_t o[RB][M];
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
                     const int ki = uld(rac[r] + w + k + m);
-                    const uint32_t own_o = (uint32_t)it.i[r] * ds + jo, o = (uint32_t)ki * ds + (col.l[m] >> 16) * ES;
-                    const uint32_t none = (uint32_t)(ki >> 31) | (uint32_t)((int32_t)(col.l[m] >> 16 ^ 0xffffu) - 1 >> 31);
-                    jump[r][m] = x(o ^ ((o ^ own_o) & none));  // (bit operations: a select became a branch)
+                    const uint32_t own_o = (uint32_t)it.i[r] * ds + jo, to = (uint32_t)ki * ds + (col.l[m] >> 16) * ES;
+                    const uint32_t none = (uint32_t)(ki >> 31) | (uint32_t)(((int32_t)(col.l[m] >> 16 ^ 0xffffu) - 1) >> 31);
+                    o[r][m] = to ^ ((to ^ own_o) & none);  // (bit operations: a select became a branch)
+                    jump[r][m] = x(o[r][m]);
+                }
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    v[r][m] = from_d2<V>(cmulc(uld(rcv[r] + k + m), col.c[m]));
+                    const bool own = o[r][m] == (uint32_t)it.i[r] * ds + jo;
+                    v[r][m].x = own ? T(0) : v[r][m].x;
+                    v[r][m].y = own ? T(0) : v[r][m].y;
                 }
         };
-        V va[RB][M], vc[RB][M];
+        V va[RB][M];
         if constexpr (RB == 1) {
             load_side();
+#pragma unroll
+            for (int m = 0; m < M; ++m) va[0][m] = uld(rav[0] + k + m);
             load_jump();
-#pragma unroll
-            for (int m = 0; m < M; ++m) va[0][m] = uld(rav[0] + k + m), vc[0][m] = uld(rav[0] + w + k + m);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (FIRST) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                V dd;
-                dd.x = (T)(di[r].x + dj.x);
-                dd.y = (T)(di[r].y - dj.y);
-                acc[r].x = acc[r].y = T(0);
-                cfma(acc[r], dd, own[r]);
-            }
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -247,22 +259,38 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int m = 0; m < M; ++m)
-                cfma(acc[r], cmulc(RB == 1 ? vc[r][m] : uld(rav[r] + w + k + m), col.c[m]), jump[r][m]);
+            for (int m = 0; m < M; ++m) cfma(acc[r], v[r][m], jump[r][m]);
     };
-    part(std::true_type{}, pre, 0);
+    if (O.self) {  // jumps that start from the element itself
+#pragma unroll 1
+        for (int k = 0; k < w; ++k) {
+            const uint32_t q = (uint32_t)(k * d + it.j);
+            const int l = (int)((uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)) >> 16);
+            const double2 c = at(O.cval, q * 16u);
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const double2 p = cmulc(uld(rcv[r] + k), c);
+                const bool own = uld(rac[r] + w + k) == it.i[r] && l == it.j;
+                dd[r].x += own ? p.x : 0.0;
+                dd[r].y += own ? p.y : 0.0;
+            }
+        }
+    }
+    part(pre, 0);
     int k = M0;
 #pragma unroll 1
     for (; k + 4 <= w; k += 4) {
         OpCols<V, 4> col;
         col.load(O, d, it.j, k);
-        part(std::false_type{}, col, k);
+        part(col, k);
     }
     if (k < w) {
         OpCols<V, 2> col;
         col.load(O, d, it.j, k);
-        part(std::false_type{}, col, k);
+        part(col, k);
     }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) cfma(acc[r], from_d2<V>(dd[r]), own[r]);
 }
 
 // Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.

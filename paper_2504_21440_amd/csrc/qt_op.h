@@ -20,12 +20,14 @@ constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
 //   diag [d]     A_ii
 //   lcol [w][d]  column of A's off-diagonal entry | column of C_c's entry << 16 (0xffff: none)
 //   aval [w][d]  A's values, state precision
-//   cval [w][d]  C_c's value, state precision
-//   rows [d]     records: columns of A [w], of the jumps [w] (-1: none), values of A [w], of the jumps [w]
+//   cval [w][d]  C_c's value, FP64 (a product of two is rounded once, as the assembled matrix rounds it)
+//   rows [d]     records: columns of A [w], of the jumps [w] (-1: none), values of A [w] (state precision), of the
+//                jumps [w] (FP64)
 // One allocation holds them, so that descriptors (kernel arguments of every CSR launch) stay short.
 struct OpForm {
     const void *mem;
-    int32_t w, pad;
+    int32_t w;
+    int32_t self;  // 1: some C_c has an entry on its diagonal, so jumps reach the element itself
 };
 
 // Byte offsets of the tables (diag at 0) for state elements of es bytes, and the bytes of all.
@@ -37,9 +39,10 @@ struct OpOffsets {
         lcol = up((uint32_t)d * 16u);
         aval = lcol + up(n * 4u);
         cval = aval + up(n * es);
-        rows = cval + up(n * es);
-        total = rows + up(n * (8u + 2u * es));
+        rows = cval + up(n * 16u);
+        total = rows + up((uint32_t)d * rec(w, es));
     }
+    static __host__ __device__ uint32_t rec(int w, uint32_t es) { return (uint32_t)w * (8u + es + 16u); }  // bytes of a row's record
     static __host__ __device__ uint32_t up(uint32_t b) { return (b + 255u) & ~255u; }
 };
 

@@ -524,8 +524,9 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
     }
     if (w > OP_MAX_W) return QT_OK;
     w = std::max(4, (w + 1) & ~1);
-    const size_t es = prec == QT_F64 ? 16 : 8, rec = (size_t)w * (8 + 2 * es);
+    const size_t es = prec == QT_F64 ? 16 : 8, rec = OpOffsets::rec(w, (uint32_t)es);
     const OpOffsets o(d, w, (uint32_t)es);
+    bool self = false;
     const size_t o_lc = o.lcol, o_av = o.aval, o_cv = o.cval, o_rec = o.rows, total = o.total;
     std::vector<char> h(total, 0);
     double2 *diag = (double2 *)h.data();
@@ -555,8 +556,10 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
             rcc[c] = has ? cs[c].idx[cs[c].ptr[i]] : -1;
             lc[(size_t)c * d + i] |= (int32_t)((uint32_t)(has ? rcc[c] : 0xffff) << 16);
             if (!has) continue;
-            put(o_cv, (size_t)c * d + i, cs[c].val[cs[c].ptr[i]]);
-            put(rcv, c, cs[c].val[cs[c].ptr[i]]);
+            const cd v = cs[c].val[cs[c].ptr[i]];
+            ((double2 *)(h.data() + o_cv))[(size_t)c * d + i] = make_double2(v.real(), v.imag());
+            ((double2 *)(h.data() + rcv))[c] = make_double2(v.real(), v.imag());
+            self = self || rcc[c] == i;
         }
     }
     if (hipMalloc(&L->op_mem, total) != hipSuccess) {  // then the matrix kernels take the problem
@@ -568,6 +571,7 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
         return set_error(QT_EDEVICE, "upload operator tables");
     L->op.mem = L->op_mem;
     L->op.w = w;
+    L->op.self = self ? 1 : 0;
     return QT_OK;
 }
 
