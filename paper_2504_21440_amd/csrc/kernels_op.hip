@@ -262,18 +262,21 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
             for (int m = 0; m < M; ++m) cfma(acc[r], v[r][m], jump[r][m]);
     };
     if (O.self) {  // jumps that start from the element itself
-#pragma unroll 1
-        for (int k = 0; k < w; ++k) {
-            const uint32_t q = (uint32_t)(k * d + it.j);
-            const int l = (int)((uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)) >> 16);
-            const double2 c = at(O.cval, q * 16u);
+        auto add = [&](int k, uint32_t l, double2 c) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
                 const double2 p = cmulc(uld(rcv[r] + k), c);
-                const bool own = uld(rac[r] + w + k) == it.i[r] && l == it.j;
+                const bool own = uld(rac[r] + w + k) == it.i[r] && (int)(l >> 16) == it.j;
                 dd[r].x += own ? p.x : 0.0;
                 dd[r].y += own ? p.y : 0.0;
             }
+        };
+#pragma unroll
+        for (int m = 0; m < M0; ++m) add(m, pre.l[m], pre.c[m]);
+#pragma unroll 1
+        for (int k = M0; k < w; ++k) {
+            const uint32_t q = (uint32_t)(k * d + it.j);
+            add(k, (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)), at(O.cval, q * 16u));
         }
     }
     part(pre, 0);
