@@ -293,7 +293,11 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
         part(col, k);
     }
 #pragma unroll
-    for (int r = 0; r < RB; ++r) cfma(acc[r], from_d2<V>(dd[r]), own[r]);
+    for (int r = 0; r < RB; ++r) {
+        cfma(acc[r], from_d2<V>(dd[r]), own[r]);
+        // rho A^dag is the conjugate of A rho on the diagonal, but their sums round one after the other
+        if (it.i[r] == it.j) acc[r].y = T(0);
+    }
 }
 
 // Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.
