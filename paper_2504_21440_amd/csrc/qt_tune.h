@@ -33,7 +33,9 @@ int dense_default_waves(int np, int32_t prec);
 // Candidate CSR shapes the autotuner measures (both matrix load kinds).  single: include the
 // XCD-contiguous block order, which only single-problem plans use: with several problems of
 // unequal step counts, an XCD whose problems have finished would sit idle while the others still
-// work through theirs.
-int csr_candidates(CsrShape *out, int max, bool single);
+// work through theirs.  fold: only the matrix load kind whose step control can fold into stage 2 (what folding
+// saves, one launch per step, is not in the stage times they are compared by).  The set does not depend on the
+// plan's present layout, so tuning twice measures the same shapes.
+int csr_candidates(CsrShape *out, int max, bool single, bool fold);
 
 }  // namespace qt

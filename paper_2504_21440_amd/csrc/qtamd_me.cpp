@@ -667,17 +667,21 @@ qt_status me_plan_create(Ctx *ctx, int32_t n, const qt_me_problem *probs, const 
 }
 
 // Launch configuration of lane `k` of the plan's CSR problems at the current shape.
-// Whether a step's control folds into the next step's stage-2 launch at matrix load kind keep: one
-// problem stored in runs of 4 entries (keep 2) with no steady-state test, over an even number of
-// steps per graph (the double-buffered record ends where it began).
+// Whether a step's control can fold into the next step's stage-2 launch: one problem with no steady-state
+// test, over an even number of steps per graph (the double-buffered record ends where it began).
+static bool may_fold(const qt_me_plan *P)
+{
+    return P->ncsr == 1 && P->h_ci[0].steady_tol2 <= 0.0 && P->graph_steps % 2 == 0;
+}
+
+// It folds at matrix load kind keep 2 (stored in runs of 4 entries), in the lane's present layout.
 // Every workgroup of the folded launch reads every block partial, so a problem of very many blocks keeps
 // the control launch: 32,768 blocks (L = 10, FP64, matrix kernels) took 259 us folded against 118 + 18 us;
 // 1,088 blocks (the same problem in operator form) 35 us against 28 + 12 us.
 constexpr int32_t FOLD_MAX_BLOCKS = 8192;
 static bool folds_control(const qt_me_plan *P, int keep)
 {
-    return P->ncsr == 1 && keep == 2 && P->h_ci[0].steady_tol2 <= 0.0 && P->graph_steps % 2 == 0 &&
-           P->h_ci[0].nblocks <= FOLD_MAX_BLOCKS;
+    return may_fold(P) && keep == 2 && P->h_ci[0].nblocks <= FOLD_MAX_BLOCKS;
 }
 
 static CsrLaunch csr_args(const qt_me_plan *P, int k = 0)
@@ -961,14 +965,10 @@ qt_status me_plan_autotune(qt_me_plan *P, int32_t reps)
     if (reps <= 0) reps = 20;
     if (P->ncsr) {
         CsrShape cand[64];
-        const int nc = csr_candidates(cand, 64, P->ncsr == 1);
+        const int nc = csr_candidates(cand, 64, P->ncsr == 1, may_fold(P));
         CsrShape best = P->shape;
         double best_ms = 1e300;
-        // The stage timing below cannot see what folding the step control into stage 2 saves (one
-        // launch per step), so a plan that can fold chooses among the shapes that fold.
-        const bool fold = folds_control(P, 2);
         for (int k = 0; k < nc; ++k) {
-            if (fold && !folds_control(P, cand[k].keep)) continue;
             qt_status st = apply_shape(P, cand[k]);
             if (st) return st;
             double ms;

@@ -88,11 +88,11 @@ int dense_default_waves(int np, int32_t prec)
     return nt * nt > 4 ? 8 : nt * nt <= 1 ? 2 : 4;
 }
 
-int csr_candidates(CsrShape *out, int max, bool single)
+int csr_candidates(CsrShape *out, int max, bool single, bool fold)
 {
     static const int lprs[] = {4, 8, 16}, rgs[] = {1, 2, 4};
     int n = 0;
-    for (int k = 0; k < 3; ++k)
+    for (int k = fold ? 2 : 0; k < 3; ++k)
         for (int x = 0; x < (single ? 2 : 1); ++x)
             for (int l : lprs)
                 for (int r : rgs)
