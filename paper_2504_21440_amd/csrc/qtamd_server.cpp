@@ -522,16 +522,19 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
         constexpr int MAX_REPLAYS = 64;  // bounds an epoch, so that new requests are admitted
         qt_status st = QT_OK;
         hipError_t e = hipSuccess;
+        // resident classes on the pool streams that no matrix-core bucket uses (without one, on the small
+        // lane's), so that a replay does not wait for a bucket's epoch
+        const int nb = std::min<int>((int)buckets.size(), Ctx::NPOOL), nfree = rruns.empty() ? 0 : Ctx::NPOOL - nb;
+        if (!rruns.empty() && !nfree) e = hipStreamWaitEvent(sa, ev, 0);
         for (int rep = 0; rep < MAX_REPLAYS && !st && e == hipSuccess; ++rep) {
             for (size_t k = 0; k < rruns.size() && !st; ++k)
                 st = res_launch(rruns[k].cls, f64, S->d_rinst, S->d_rctl, S->d_order + rruns[k].start, rruns[k].count,
-                                K, 0, ctx->pool[(buckets.size() + k) % Ctx::NPOOL]);
+                                K, 0, nfree ? ctx->pool[nb + (int)k % nfree] : sa);
             for (int l : {1, 3})
                 if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l >= 2, sa);
             if (!st && (!bi[1].empty() || !bi[3].empty()))
                 e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
-            if (!rruns.empty())
-                for (int b = 0; b < Ctx::NPOOL && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[b]);
+            for (int b = 0; b < nfree && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[nb + b]);
             if (!st && e == hipSuccess && !rruns.empty())
                 e = hipMemcpyAsync(S->h_rctl, S->d_rctl, sizeof(ResCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
             if (e == hipSuccess) e = hipStreamSynchronize(sa);
