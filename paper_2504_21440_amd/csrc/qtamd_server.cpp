@@ -11,13 +11,12 @@
 // work overlaps on the device with whatever else is resident.  A request's arithmetic does not
 // depend on what else is resident: its blocks, reductions and step decisions are its own.
 //
-// CSR requests that are not resident run in four lanes, each with its own block table and epoch graphs:
-// large (0: matrix kernels, 2: operator form) on the context's stream, small ones (1, 3) on its auxiliary
-// stream.  A small problem's
-// step costs a few microseconds of launch latency, a large one's far more, so in one shared table
-// a stiff small request would advance only at the large ones' pace.  While the large lane's epoch
-// runs, the small lane replays its own epoch graph, until the large lane finishes or no small
-// request is left running.
+// CSR requests that are not resident run in three lanes, each with its own block table and epoch graphs:
+// large ones (0: matrix kernels, 2: operator form) on the context's stream, small ones (1) on its auxiliary
+// stream; the operator form takes no small one.  A small problem's step costs a few microseconds of launch
+// latency, a large one's far more, so in one shared table a stiff small request would advance only at the
+// large ones' pace.  While the large lanes' epoch runs, the small lane replays its own epoch graph, until the
+// large ones finish or no small request is left running.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -80,6 +79,11 @@ struct PoolAlloc {
     }
 };
 
+constexpr int N_LANES = 3;
+// Liouville rows up to which a CSR request runs in the small lane (d <= 128)
+constexpr int64_t SMALL_LANE_ROWS = 16384;
+static_assert((int64_t)OP_MIN_D * OP_MIN_D > SMALL_LANE_ROWS, "operator-form requests are all large");
+
 struct Request {
     uint64_t ticket = 0;
     int32_t slot = -1;
@@ -130,9 +134,9 @@ struct qt_server {
         size_t blk_cap = 0;           // entries of d_bi / d_br (a power of two, fixed at creation)
         std::map<int, EpochGraph> graphs;
     };
-    // 0: large Liouvillians (context stream), 1: small ones (auxiliary stream); 2, 3: the same of the requests
-    // that the operator-form kernels run
-    Lane lanes[4];
+    // 0: large Liouvillians (context stream), 1: small ones (auxiliary stream), 2: those that the operator-form
+    // kernels run (context stream; all of them are large)
+    Lane lanes[qt::N_LANES];
     qt::CsrCtl *h_cctl = nullptr;   // pinned
     qt::DenseCtl *h_dctl = nullptr; // pinned
     qt::ResCtl *h_rctl = nullptr;   // pinned
@@ -382,9 +386,6 @@ static void drop_graphs(qt_server::Lane &ln)
     ln.graphs.clear();
 }
 
-// Liouville rows up to which a CSR request runs in the small lane (d <= 128)
-constexpr int64_t SMALL_LANE_ROWS = 16384;
-
 // Uploads a lane's block table and control list and launches its epoch graph (capturing it on
 // first use of this grid size) on stream s.
 // op: run by the operator-form kernels.
@@ -449,12 +450,12 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     const bool f64 = S->prec == QT_F64;
     const int K = std::max(1, S->cfg.steps_per_epoch);
     // ---- CSR slots: one block table per lane ----
-    std::vector<int32_t> bi[4], br[4], csr_slots[4];
+    std::vector<int32_t> bi[N_LANES], br[N_LANES], csr_slots[N_LANES];
     const int rpb = csr_rows_per_block(S->shape.lpr, S->shape.rg);
     for (uint64_t tk : S->active) {
         Request &R = S->reqs[tk];
         if (R.dense || R.res >= 0) continue;
-        const int l = ((int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0) + (R.op ? 2 : 0);
+        const int l = R.op ? 2 : (int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0;
         for (int32_t b = 0; b < R.nblocks; ++b) {
             bi[l].push_back(R.slot);
             br[l].push_back(R.op ? b : b * rpb);
@@ -508,7 +509,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     if (!bi[0].empty() || !bi[2].empty()) {
         qt_status st = QT_OK;
         for (int l : {0, 2})
-            if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l >= 2, s);
+            if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l == 2, s);
         if (st) {
             if (ev) (void)hipEventDestroy(ev);
             return st;
@@ -517,7 +518,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
         QT_HIP(hipEventRecord(big_done, s));
     }
     // ---- small CSR lane and resident requests: replayed while the large lane runs and one of them still steps ----
-    if (!bi[1].empty() || !bi[3].empty() || !rruns.empty()) {
+    if (!bi[1].empty() || !rruns.empty()) {
         hipStream_t sa = ctx->aux;
         constexpr int MAX_REPLAYS = 64;  // bounds an epoch, so that new requests are admitted
         qt_status st = QT_OK;
@@ -530,9 +531,8 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
             for (size_t k = 0; k < rruns.size() && !st; ++k)
                 st = res_launch(rruns[k].cls, f64, S->d_rinst, S->d_rctl, S->d_order + rruns[k].start, rruns[k].count,
                                 K, 0, nfree ? ctx->pool[nb + (int)k % nfree] : sa);
-            for (int l : {1, 3})
-                if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l >= 2, sa);
-            if (!st && (!bi[1].empty() || !bi[3].empty()))
+            if (!st && !bi[1].empty()) st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, false, sa);
+            if (!st && !bi[1].empty())
                 e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
             for (int b = 0; b < nfree && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[nb + b]);
             if (!st && e == hipSuccess && !rruns.empty())
@@ -540,8 +540,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
             if (e == hipSuccess) e = hipStreamSynchronize(sa);
             if (!big_done || hipEventQuery(big_done) != hipErrorNotReady) break;
             bool running = false;
-            for (int l : {1, 3})
-                for (int32_t slot : csr_slots[l]) running = running || S->h_cctl[slot].status == ST_RUNNING;
+            for (int32_t slot : csr_slots[1]) running = running || S->h_cctl[slot].status == ST_RUNNING;
             for (auto &x : rlist) running = running || S->h_rctl[S->reqs[x.second].slot].status == ST_RUNNING;
             if (!running) break;
         }
@@ -645,7 +644,7 @@ static qt_status check_cfg(const qt_server_cfg *cfg)
 
 // Lays out the server's device memory in S->arena and returns the offsets through the members.
 struct ServerLayout {
-    size_t pool, cinst, cctl, dinst, dctl, order, rinst, rctl, ilist[4], counts[4], bi[4], br[4];
+    size_t pool, cinst, cctl, dinst, dctl, order, rinst, rctl, ilist[N_LANES], counts[N_LANES], bi[N_LANES], br[N_LANES];
 };
 static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap)
 {
@@ -659,7 +658,7 @@ static ServerLayout server_layout(Arena &A, const qt_server_cfg *cfg, size_t cap
     L.order = A.reserve(sizeof(int32_t) * ns);
     L.rinst = A.reserve(sizeof(ResInst) * ns);
     L.rctl = A.reserve(sizeof(ResCtl) * ns);
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < N_LANES; ++k) {
         L.ilist[k] = A.reserve(sizeof(int32_t) * ns);
         L.counts[k] = A.reserve(sizeof(int32_t) * 2);
         L.bi[k] = A.reserve(4 * cap);
@@ -695,7 +694,7 @@ static qt_status server_create(Ctx *ctx, const qt_server_cfg *cfg, void *ws, siz
     S->d_order = (int32_t *)A.at(Ly.order);
     S->d_rinst = (ResInst *)A.at(Ly.rinst);
     S->d_rctl = (ResCtl *)A.at(Ly.rctl);
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < N_LANES; ++k) {
         auto &ln = S->lanes[k];
         ln.d_ilist = (int32_t *)A.at(Ly.ilist[k]);
         ln.d_counts = (int32_t *)A.at(Ly.counts[k]);
