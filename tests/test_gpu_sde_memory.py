@@ -66,3 +66,20 @@ def test_master_equations_with_several_measured_operators(ctx, d, m, ntraj, prec
     ref = oracle.smesolve(H, C, S, rho, tl, e, 3, 41, 2e-3)
     res = qt.smesolve(ctx, H, C, S, rho, tl, e, ntraj, 41, 2e-3, options=qt.opts(precision=prec), want_traj=True)
     _check(res, ref, prec, 3)
+
+
+@pytest.mark.parametrize("prec", [qt.F64, qt.MIXED])
+@pytest.mark.parametrize("d", [40, 600, 2100])
+def test_no_measured_operator(ctx, d, prec):
+    """A closed system: Euler steps of the renormalised ket, the oracle's to rounding."""
+    print(f"[gpu] sde memory SSE d={d} m=0 prec={prec}", flush=True)
+    g = np.random.default_rng(d)
+    v = 0.3 * g.uniform(-1, 1, d - 1)
+    H = sp.diags([g.uniform(-1, 1, d), v, v], [0, 1, -1], format="csr").astype(complex)
+    psi = g.normal(size=d) + 1j * g.normal(size=d)
+    psi /= np.linalg.norm(psi)
+    tl, e = np.linspace(0.0, 0.3, 4), [sp.diags(np.linspace(0, 1, d)).astype(complex).tocsr()]
+    ref = oracle.ssesolve(H, [], psi, tl, e, 2, 23, 2e-3)
+    res = qt.ssesolve(ctx, H, [], psi, tl, e, 2, 23, 2e-3, options=qt.opts(precision=prec), want_traj=True)
+    assert np.abs(res["expect_tr"] - ref["expect_tr"]).max() <= (1e-8 if prec == qt.F64 else 1e-4)
+    assert res["stats"]["status"] == 0
