@@ -28,6 +28,8 @@
 // the rate: after t = 100 with C = sqrt(0.1) n (d = 160) populations had drifted by 1e-4.  Everything else of a
 // step -- stage combinations, error partials, control, expectation values -- is that of kernels_csr.hip, on
 // the same descriptors, with op_blocks(d) partials a problem.
+#include <type_traits>
+
 #include "csr_kernels.h"
 
 namespace qt {
@@ -130,7 +132,7 @@ template <typename P> __device__ __forceinline__ void keep(P &p) { asm volatile(
 
 // A problem's tables (es: bytes of a state element), their descriptor read at once.
 struct OpTabs {
-    int w, self;
+    int w;
     const double2 *diag;
     const int32_t *lcol;
     const void *aval, *rows;
@@ -139,8 +141,7 @@ struct OpTabs {
     {
         const char *mem = (const char *)O.mem;
         w = O.w;
-        self = O.self;
-        keep(w), keep(self), keep(mem);
+        keep(w), keep(mem);
         const OpOffsets o(d, w, es);
         diag = (const double2 *)mem;
         lcol = (const int32_t *)(mem + o.lcol);
@@ -173,7 +174,7 @@ template <typename V, int M> struct OpCols {
 // the sums stays in registers.  pre: the first M0 entries (the first group).  One row (small problems, bound
 // by the latency of a wave): every source of a group is requested before its first sum; more: up to four
 // entries of RB rows in flight.
-template <typename T, int RB, int M0, typename X>
+template <typename T, int RB, int M0, bool SELF, typename X>
 __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> &it, double2 dj,
                                        const OpCols<typename vec2<T>::type, M0> &pre, X x,
                                        typename vec2<T>::type (&acc)[RB])
@@ -199,8 +200,9 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
         own[r] = x((uint32_t)it.i[r] * ds + jo);
         acc[r].x = acc[r].y = T(0);
     }
-    auto part = [&](const auto &col, int k) {
+    auto part = [&](auto first, const auto &col, int k) {
         constexpr int M = sizeof(col.l) / 4;
+        constexpr bool FIRST = decltype(first)::value;
         V up[RB][M], side[RB][M], jump[RB][M];
         // A rho: the column's other rows
 #pragma unroll
@@ -214,7 +216,7 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
                 for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (col.l[m] & 0xffffu) * ES);
         };
         // the jumps; an element without one takes itself, times zero, as does one whose jump starts from the element
-        // (counted in dd)
+        // (counted in dd: SELF)
         V v[RB][M];
         auto load_jump = [&]() {
             uint32_t o[RB][M];
@@ -233,9 +235,11 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
                     v[r][m] = from_d2<V>(cmulc(uld(rcv[r] + k + m), col.c[m]));
-                    const bool own = o[r][m] == (uint32_t)it.i[r] * ds + jo;
-                    v[r][m].x = own ? T(0) : v[r][m].x;
-                    v[r][m].y = own ? T(0) : v[r][m].y;
+                    if constexpr (SELF) {
+                        const bool own = o[r][m] == (uint32_t)it.i[r] * ds + jo;
+                        v[r][m].x = own ? T(0) : v[r][m].x;
+                        v[r][m].y = own ? T(0) : v[r][m].y;
+                    }
                 }
         };
         V va[RB][M];
@@ -245,6 +249,10 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
             for (int m = 0; m < M; ++m) va[0][m] = uld(rav[0] + k + m);
             load_jump();
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (FIRST) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) cfma(acc[r], from_d2<V>(dd[r]), own[r]);
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -261,7 +269,7 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 #pragma unroll
             for (int m = 0; m < M; ++m) cfma(acc[r], v[r][m], jump[r][m]);
     };
-    if (O.self) {  // jumps that start from the element itself
+    if constexpr (SELF) {  // jumps that start from the element itself
         auto add = [&](int k, uint32_t l, double2 c) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
@@ -279,29 +287,26 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
             add(k, (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)), at(O.cval, q * 16u));
         }
     }
-    part(pre, 0);
+    part(std::true_type{}, pre, 0);
     int k = M0;
 #pragma unroll 1
     for (; k + 4 <= w; k += 4) {
         OpCols<V, 4> col;
         col.load(O, d, it.j, k);
-        part(col, k);
+        part(std::false_type{}, col, k);
     }
     if (k < w) {
         OpCols<V, 2> col;
         col.load(O, d, it.j, k);
-        part(col, k);
+        part(std::false_type{}, col, k);
     }
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        cfma(acc[r], from_d2<V>(dd[r]), own[r]);
-        // rho A^dag is the conjugate of A rho on the diagonal, but their sums round one after the other
+    for (int r = 0; r < RB; ++r)  // rho A^dag is the conjugate of A rho on the diagonal, but their sums round in turn
         if (it.i[r] == it.j) acc[r].y = T(0);
-    }
 }
 
 // Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.
-template <typename T, int RB, int M0>
+template <typename T, int RB, int M0, bool SELF>
 __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, int blk, int which)
 {
     using V = typename vec2<T>::type;
@@ -323,13 +328,13 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
         const double2 dj = gld(O.diag + it.j);
         V acc[RB];
         if (which)
-            op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) {
+            op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) {
                 V v = at((const V *)y, o);
                 caxpy(v, th0, at((const V *)k1, o));
                 return v;
             }, acc);
         else
-            op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) { return at(x0, o); }, acc);
+            op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) { return at(x0, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -371,7 +376,7 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
 }
 
 // One Runge-Kutta stage S (2..7), uniform over the launch.
-template <typename T, int RB, int M0>
+template <typename T, int RB, int M0, bool SELF>
 __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C, int blk, int S)
 {
     using V = typename vec2<T>::type;
@@ -419,7 +424,7 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
             if (RB == 1 || S == 7) ynr = at(ynew, row);
         };
         if constexpr (RB == 1) operands(0);
-        op_sum<T, RB, M0>(O, d, it, dj, pre, [&](uint32_t o) { return at(xin, o); }, acc);
+        op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) { return at(xin, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -494,20 +499,20 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
 
 // The stage or starting step `what` of one workgroup: the row count by the dimension, the entries requested
 // at once by the table width (small problems).
-template <typename T, bool INIT, bool SMALL>
+template <typename T, bool INIT, bool SMALL, bool SELF>
 __device__ __forceinline__ void op_body(const CsrInst &I, const CsrCtl *C, int blk, int what)
 {
     if constexpr (SMALL) {
         if (I.op.w >= 8) {
-            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 8>(I, C, blk, what);
-            else op_stage_body<T, OP_ROWS_SMALL, 8>(I, C, blk, what);
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 8, SELF>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 8, SELF>(I, C, blk, what);
         } else {
-            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 4>(I, C, blk, what);
-            else op_stage_body<T, OP_ROWS_SMALL, 4>(I, C, blk, what);
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 4, SELF>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 4, SELF>(I, C, blk, what);
         }
     } else {
-        if constexpr (INIT) op_init_body<T, OP_ROWS, 4>(I, C, blk, what);
-        else op_stage_body<T, OP_ROWS, 4>(I, C, blk, what);
+        if constexpr (INIT) op_init_body<T, OP_ROWS, 4, SELF>(I, C, blk, what);
+        else op_stage_body<T, OP_ROWS, 4, SELF>(I, C, blk, what);
     }
 }
 
@@ -520,72 +525,75 @@ __device__ __forceinline__ int op_block(int n)
 
 // what: 0 / 1 the starting-step evaluations, 2..7 a stage.  ONE: one problem, descriptor by value (SMALL: of up
 // to OP_SMALL_D); otherwise the block table (bi: problem, br: its block).  n: the grid, for the XCD-contiguous
-// order (a row's sources are then mostly rows of the same XCD's L2), 0: the launch order.
-template <typename T, bool SMALL, bool ONE, bool INIT>
-__global__ __launch_bounds__(CSR_THREADS) void k_op(const CsrInst *__restrict__ insts, const CsrInst one,
+// order (a row's sources are then mostly rows of the same XCD's L2), 0: the launch order.  SELF: some problem of
+// the launch has a diagonal entry in a channel.  (The sums of the others are the same either way; the mask and
+// its registers cost chains of lowering operators 3 to 4%.)
+// The complex64 stages are held to 128 registers, four waves a SIMD (130 otherwise).
+template <typename T, bool SMALL, bool ONE, bool INIT, bool SELF>
+__global__ __launch_bounds__(CSR_THREADS, sizeof(T) == 4 && !INIT ? 4 : 1) void k_op(const CsrInst *__restrict__ insts, const CsrInst one,
                                                     const CsrCtl *__restrict__ ctls, const int32_t *__restrict__ bi,
                                                     const int32_t *__restrict__ br, int n,
                                                     const int32_t *__restrict__ bound, int what)
 {
     const int lb = op_block(n);
     if constexpr (ONE) {
-        op_body<T, INIT, SMALL>(one, ctls, lb, what);
+        op_body<T, INIT, SMALL, SELF>(one, ctls, lb, what);
     } else {
         if (bound && lb >= bound[0]) return;
         const int ii = bi[lb], blk = br[lb];
-        if (insts[ii].d <= OP_SMALL_D) op_body<T, INIT, true>(insts[ii], ctls + ii, blk, what);
-        else op_body<T, INIT, false>(insts[ii], ctls + ii, blk, what);
+        if (insts[ii].d <= OP_SMALL_D) op_body<T, INIT, true, SELF>(insts[ii], ctls + ii, blk, what);
+        else op_body<T, INIT, false, SELF>(insts[ii], ctls + ii, blk, what);
     }
 }
 
 // Stage 2 with the previous step's control folded in, as k_csr_stage2_ctl.
-template <typename T, bool SMALL>
+template <typename T, bool SMALL, bool SELF>
 __global__ __launch_bounds__(CSR_THREADS) void k_op_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
                                                                CsrCtl *__restrict__ wr, int n)
 {
     using V = typename vec2<T>::type;
     __shared__ CsrCtl nsh;
     if (!ctl_fold<V, false>(one, rd, wr, nsh, nullptr)) return;
-    op_body<T, false, SMALL>(one, &nsh, op_block(n), 2);
+    op_body<T, false, SMALL, SELF>(one, &nsh, op_block(n), 2);
 }
 
-template <typename T, bool SMALL, bool ONE> static void op_launch_t(const CsrArgs &a, int what)
+template <typename T, bool SMALL, bool ONE, bool SELF> static void op_launch_t(const CsrArgs &a, int what)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
     const int n = a.xcd ? a.nblk : 0;
 #define QT_ARGS a.insts, a.one, a.ctls, a.bi, a.br, n, a.bound, what
-    if (what < 2) hipLaunchKernelGGL((k_op<T, SMALL, ONE, true>), g, t, 0, a.s, QT_ARGS);
-    else hipLaunchKernelGGL((k_op<T, SMALL, ONE, false>), g, t, 0, a.s, QT_ARGS);
+    if (what < 2) hipLaunchKernelGGL((k_op<T, SMALL, ONE, true, SELF>), g, t, 0, a.s, QT_ARGS);
+    else hipLaunchKernelGGL((k_op<T, SMALL, ONE, false, SELF>), g, t, 0, a.s, QT_ARGS);
 #undef QT_ARGS
 }
 
-template <typename T> static void op_launch(const CsrArgs &a, int what)
+template <typename T, bool SELF> static void op_launch(const CsrArgs &a, int what)
 {
-    if (!a.use_one) op_launch_t<T, false, false>(a, what);
-    else if (a.one.d <= OP_SMALL_D) op_launch_t<T, true, true>(a, what);
-    else op_launch_t<T, false, true>(a, what);
+    if (!a.use_one) op_launch_t<T, false, false, SELF>(a, what);
+    else if (a.one.d <= OP_SMALL_D) op_launch_t<T, true, true, SELF>(a, what);
+    else op_launch_t<T, false, true, SELF>(a, what);
 }
 
-template <typename T> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
+template <typename T, bool SELF> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
     const int n = a.xcd ? a.nblk : 0;
-    if (a.one.d <= OP_SMALL_D) hipLaunchKernelGGL((k_op_stage2_ctl<T, true>), g, t, 0, a.s, a.one, rd, wr, n);
-    else hipLaunchKernelGGL((k_op_stage2_ctl<T, false>), g, t, 0, a.s, a.one, rd, wr, n);
+    if (a.one.d <= OP_SMALL_D) hipLaunchKernelGGL((k_op_stage2_ctl<T, true, SELF>), g, t, 0, a.s, a.one, rd, wr, n);
+    else hipLaunchKernelGGL((k_op_stage2_ctl<T, false, SELF>), g, t, 0, a.s, a.one, rd, wr, n);
 }
 
 void op_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last)
 {
-    for (int what = first; what <= last; ++what) {
-        if (L.f64) op_launch<double>(a, what);
-        else op_launch<float>(a, what);
-    }
+    const auto launch = L.f64 ? (L.op_self ? op_launch<double, true> : op_launch<double, false>)
+                              : (L.op_self ? op_launch<float, true> : op_launch<float, false>);
+    for (int what = first; what <= last; ++what) launch(a, what);
 }
 
 void op_stage2_ctl(const CsrLaunch &L, const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
 {
-    if (L.f64) op_ctl<double>(a, rd, wr);
-    else op_ctl<float>(a, rd, wr);
+    const auto launch = L.f64 ? (L.op_self ? op_ctl<double, true> : op_ctl<double, false>)
+                              : (L.op_self ? op_ctl<float, true> : op_ctl<float, false>);
+    launch(a, rd, wr);
 }
 
 }  // namespace qt

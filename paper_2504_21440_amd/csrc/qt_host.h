@@ -135,6 +135,7 @@ struct CsrLaunch {
     const int32_t *bound = nullptr, *ibound = nullptr;
     const CsrInst *one_host = nullptr;           // host copy of the descriptor when ninst == 1
     bool op = false;  // every problem of the launch has operator tables: kernels_op.hip
+    bool op_self = false;  // and some problem's channels have diagonal entries
     bool td = false;  // some problem has a time-dependent Liouvillian: the SpMV kernels weight its terms
     // One problem with runs of 4 stored entries and no steady-state test: the step control
     // is folded into the next step's stage-2 launch (csr_launch_step).
