@@ -130,14 +130,14 @@ __device__ __forceinline__ double uniform(double v)
 // first use, one round trip to memory after the other.
 template <typename P> __device__ __forceinline__ void keep(P &p) { asm volatile("" : "+s"(p)); }
 
-// A problem's tables (es: bytes of a state element), their descriptor read at once.
+// A problem's tables (es: bytes of a state element; SHORT: the channels' column entries in FP32), their descriptor
+// read at once.
 struct OpTabs {
     int w;
     const double2 *diag;
     const int32_t *lcol;
-    const void *aval, *rows;
-    const double2 *cval;
-    __device__ __forceinline__ OpTabs(const OpForm &O, int d, uint32_t es)
+    const void *aval, *cval, *rows;
+    __device__ __forceinline__ OpTabs(const OpForm &O, int d, uint32_t es, bool shorts)
     {
         const char *mem = (const char *)O.mem;
         w = O.w;
@@ -146,15 +146,16 @@ struct OpTabs {
         diag = (const double2 *)mem;
         lcol = (const int32_t *)(mem + o.lcol);
         aval = mem + o.aval;
-        cval = (const double2 *)(mem + o.cval);
+        cval = mem + (shorts ? o.cshort : o.cval);
         rows = mem + o.rows;
     }
 };
 
 // M entries of this lane's column, from entry k on.
-template <typename V, int M> struct OpCols {
+template <typename V, int M, int K> struct OpCols {
+    using CV = typename std::conditional<(K & OP_SHORT) != 0, float2, double2>::type;
     V a[M];         // conj A_jl
-    double2 c[M];   // C_c's value
+    CV c[M];        // C_c's value
     uint32_t l[M];  // their columns
     __device__ __forceinline__ void load(const OpTabs &O, int d, int j, int k)
     {
@@ -164,7 +165,7 @@ template <typename V, int M> struct OpCols {
             l[m] = (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u));
             a[m] = at((const V *)O.aval, q * (uint32_t)sizeof(V));
             a[m].y = -a[m].y;
-            c[m] = at(O.cval, q * 16u);
+            c[m] = at((const CV *)O.cval, q * (uint32_t)sizeof(CV));
         }
     }
 };
@@ -174,9 +175,9 @@ template <typename V, int M> struct OpCols {
 // the sums stays in registers.  pre: the first M0 entries (the first group).  One row (small problems, bound
 // by the latency of a wave): every source of a group is requested before its first sum; more: up to four
 // entries of RB rows in flight.
-template <typename T, int RB, int M0, bool SELF, typename X>
+template <typename T, int RB, int M0, int K, typename X>
 __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> &it, double2 dj,
-                                       const OpCols<typename vec2<T>::type, M0> &pre, X x,
+                                       const OpCols<typename vec2<T>::type, M0, K> &pre, X x,
                                        typename vec2<T>::type (&acc)[RB])
 {
     using V = typename vec2<T>::type;
@@ -216,7 +217,7 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
                 for (int m = 0; m < M; ++m) side[r][m] = x((uint32_t)it.i[r] * ds + (col.l[m] & 0xffffu) * ES);
         };
         // the jumps; an element without one takes itself, times zero, as does one whose jump starts from the element
-        // (counted in dd: SELF)
+        // (counted in dd: OP_SELF)
         V v[RB][M];
         auto load_jump = [&]() {
             uint32_t o[RB][M];
@@ -234,8 +235,8 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
             for (int r = 0; r < RB; ++r)
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
-                    v[r][m] = from_d2<V>(cmulc(uld(rcv[r] + k + m), col.c[m]));
-                    if constexpr (SELF) {
+                    v[r][m] = from_d2<V>(cmulc(uld(rcv[r] + k + m), to_d2(col.c[m])));
+                    if constexpr ((K & OP_SELF) != 0) {
                         const bool own = o[r][m] == (uint32_t)it.i[r] * ds + jo;
                         v[r][m].x = own ? T(0) : v[r][m].x;
                         v[r][m].y = own ? T(0) : v[r][m].y;
@@ -269,7 +270,7 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 #pragma unroll
             for (int m = 0; m < M; ++m) cfma(acc[r], v[r][m], jump[r][m]);
     };
-    if constexpr (SELF) {  // jumps that start from the element itself
+    if constexpr ((K & OP_SELF) != 0) {  // jumps that start from the element itself
         auto add = [&](int k, uint32_t l, double2 c) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
@@ -280,23 +281,24 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
             }
         };
 #pragma unroll
-        for (int m = 0; m < M0; ++m) add(m, pre.l[m], pre.c[m]);
+        for (int m = 0; m < M0; ++m) add(m, pre.l[m], to_d2(pre.c[m]));
 #pragma unroll 1
         for (int k = M0; k < w; ++k) {
             const uint32_t q = (uint32_t)(k * d + it.j);
-            add(k, (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)), at(O.cval, q * 16u));
+            add(k, (uint32_t)gld((const int32_t *)((const char *)O.lcol + q * 4u)),
+                at((const double2 *)O.cval, q * 16u));
         }
     }
     part(std::true_type{}, pre, 0);
     int k = M0;
 #pragma unroll 1
     for (; k + 4 <= w; k += 4) {
-        OpCols<V, 4> col;
+        OpCols<V, 4, K> col;
         col.load(O, d, it.j, k);
         part(std::false_type{}, col, k);
     }
     if (k < w) {
-        OpCols<V, 2> col;
+        OpCols<V, 2, K> col;
         col.load(O, d, it.j, k);
         part(std::false_type{}, col, k);
     }
@@ -306,7 +308,7 @@ __device__ __forceinline__ void op_sum(const OpTabs &O, int d, const OpItem<RB> 
 }
 
 // Starting step: which = 0 the first evaluation (k1 = L rho0, y <- rho0), 1 the second.
-template <typename T, int RB, int M0, bool SELF>
+template <typename T, int RB, int M0, int K>
 __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, int blk, int which)
 {
     using V = typename vec2<T>::type;
@@ -321,20 +323,20 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
     V *__restrict__ y = uniform_ptr((V *)I.Y[0]);
     V *__restrict__ k1 = uniform_ptr((V *)I.K[0]);
     double sa = 0.0, sb = 0.0;
-    const OpTabs O(I.op, d, sizeof(V));
+    const OpTabs O(I.op, d, sizeof(V), (K & OP_SHORT) != 0);
     if (it.i0 < d) {
-        OpCols<V, M0> pre;
+        OpCols<V, M0, K> pre;
         pre.load(O, d, it.j, 0);
         const double2 dj = gld(O.diag + it.j);
         V acc[RB];
         if (which)
-            op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) {
+            op_sum<T, RB, M0, K>(O, d, it, dj, pre, [&](uint32_t o) {
                 V v = at((const V *)y, o);
                 caxpy(v, th0, at((const V *)k1, o));
                 return v;
             }, acc);
         else
-            op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) { return at(x0, o); }, acc);
+            op_sum<T, RB, M0, K>(O, d, it, dj, pre, [&](uint32_t o) { return at(x0, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -376,7 +378,7 @@ __device__ __forceinline__ void op_init_body(const CsrInst &I, const CsrCtl *C, 
 }
 
 // One Runge-Kutta stage S (2..7), uniform over the launch.
-template <typename T, int RB, int M0, bool SELF>
+template <typename T, int RB, int M0, int K>
 __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C, int blk, int S)
 {
     using V = typename vec2<T>::type;
@@ -387,10 +389,10 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
     V *k2 = (V *)I.ks[0], *k3 = (V *)I.ks[1], *k4 = (V *)I.ks[2], *k5 = (V *)I.ks[3], *k6 = (V *)I.ks[4];
     keep(d), keep(Y0), keep(Y1), keep(K0), keep(K1), keep(ys0), keep(ys1);
     keep(k2), keep(k3), keep(k4), keep(k5), keep(k6);
-    const OpTabs O(I.op, d, sizeof(V));
+    const OpTabs O(I.op, d, sizeof(V), (K & OP_SHORT) != 0);
     // the column's first entries do not depend on the control record: in flight beside it
     const OpItem<RB> it(blk, d);
-    OpCols<V, M0> pre;
+    OpCols<V, M0, K> pre;
     pre.load(O, d, it.j, 0);
     const double2 dj = gld(O.diag + it.j);
     int status = uniform(C->status), phase = uniform(C->phase), p = uniform(C->parity);
@@ -424,7 +426,7 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
             if (RB == 1 || S == 7) ynr = at(ynew, row);
         };
         if constexpr (RB == 1) operands(0);
-        op_sum<T, RB, M0, SELF>(O, d, it, dj, pre, [&](uint32_t o) { return at(xin, o); }, acc);
+        op_sum<T, RB, M0, K>(O, d, it, dj, pre, [&](uint32_t o) { return at(xin, o); }, acc);
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             if (!it.has(r, d)) continue;
@@ -499,20 +501,20 @@ __device__ __forceinline__ void op_stage_body(const CsrInst &I, const CsrCtl *C,
 
 // The stage or starting step `what` of one workgroup: the row count by the dimension, the entries requested
 // at once by the table width (small problems).
-template <typename T, bool INIT, bool SMALL, bool SELF>
+template <typename T, bool INIT, bool SMALL, int K>
 __device__ __forceinline__ void op_body(const CsrInst &I, const CsrCtl *C, int blk, int what)
 {
     if constexpr (SMALL) {
         if (I.op.w >= 8) {
-            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 8, SELF>(I, C, blk, what);
-            else op_stage_body<T, OP_ROWS_SMALL, 8, SELF>(I, C, blk, what);
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 8, K>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 8, K>(I, C, blk, what);
         } else {
-            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 4, SELF>(I, C, blk, what);
-            else op_stage_body<T, OP_ROWS_SMALL, 4, SELF>(I, C, blk, what);
+            if constexpr (INIT) op_init_body<T, OP_ROWS_SMALL, 4, K>(I, C, blk, what);
+            else op_stage_body<T, OP_ROWS_SMALL, 4, K>(I, C, blk, what);
         }
     } else {
-        if constexpr (INIT) op_init_body<T, OP_ROWS, 4, SELF>(I, C, blk, what);
-        else op_stage_body<T, OP_ROWS, 4, SELF>(I, C, blk, what);
+        if constexpr (INIT) op_init_body<T, OP_ROWS, 4, K>(I, C, blk, what);
+        else op_stage_body<T, OP_ROWS, 4, K>(I, C, blk, what);
     }
 }
 
@@ -525,11 +527,12 @@ __device__ __forceinline__ int op_block(int n)
 
 // what: 0 / 1 the starting-step evaluations, 2..7 a stage.  ONE: one problem, descriptor by value (SMALL: of up
 // to OP_SMALL_D); otherwise the block table (bi: problem, br: its block).  n: the grid, for the XCD-contiguous
-// order (a row's sources are then mostly rows of the same XCD's L2), 0: the launch order.  SELF: some problem of
-// the launch has a diagonal entry in a channel.  (The sums of the others are the same either way; the mask and
-// its registers cost chains of lowering operators 3 to 4%.)
+// order (a row's sources are then mostly rows of the same XCD's L2), 0: the launch order.  K: OP_SELF if
+// some problem of the launch has a diagonal entry in a channel, OP_SHORT if all have short column entries.  (The
+// sums of the others are the same either way; the mask and its registers cost chains of lowering operators 3 to
+// 4%, 16-byte column entries 16 chains of L = 8 5%.)
 // The complex64 stages are held to 128 registers, four waves a SIMD (130 otherwise).
-template <typename T, bool SMALL, bool ONE, bool INIT, bool SELF>
+template <typename T, bool SMALL, bool ONE, bool INIT, int K>
 __global__ __launch_bounds__(CSR_THREADS, sizeof(T) == 4 && !INIT ? 4 : 1) void k_op(const CsrInst *__restrict__ insts, const CsrInst one,
                                                     const CsrCtl *__restrict__ ctls, const int32_t *__restrict__ bi,
                                                     const int32_t *__restrict__ br, int n,
@@ -537,62 +540,65 @@ __global__ __launch_bounds__(CSR_THREADS, sizeof(T) == 4 && !INIT ? 4 : 1) void 
 {
     const int lb = op_block(n);
     if constexpr (ONE) {
-        op_body<T, INIT, SMALL, SELF>(one, ctls, lb, what);
+        op_body<T, INIT, SMALL, K>(one, ctls, lb, what);
     } else {
         if (bound && lb >= bound[0]) return;
         const int ii = bi[lb], blk = br[lb];
-        if (insts[ii].d <= OP_SMALL_D) op_body<T, INIT, true, SELF>(insts[ii], ctls + ii, blk, what);
-        else op_body<T, INIT, false, SELF>(insts[ii], ctls + ii, blk, what);
+        if (insts[ii].d <= OP_SMALL_D) op_body<T, INIT, true, K>(insts[ii], ctls + ii, blk, what);
+        else op_body<T, INIT, false, K>(insts[ii], ctls + ii, blk, what);
     }
 }
 
 // Stage 2 with the previous step's control folded in, as k_csr_stage2_ctl.
-template <typename T, bool SMALL, bool SELF>
+template <typename T, bool SMALL, int K>
 __global__ __launch_bounds__(CSR_THREADS) void k_op_stage2_ctl(const CsrInst one, const CsrCtl *__restrict__ rd,
                                                                CsrCtl *__restrict__ wr, int n)
 {
     using V = typename vec2<T>::type;
     __shared__ CsrCtl nsh;
     if (!ctl_fold<V, false>(one, rd, wr, nsh, nullptr)) return;
-    op_body<T, false, SMALL, SELF>(one, &nsh, op_block(n), 2);
+    op_body<T, false, SMALL, K>(one, &nsh, op_block(n), 2);
 }
 
-template <typename T, bool SMALL, bool ONE, bool SELF> static void op_launch_t(const CsrArgs &a, int what)
+template <typename T, bool SMALL, bool ONE, int K> static void op_launch_t(const CsrArgs &a, int what)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
     const int n = a.xcd ? a.nblk : 0;
 #define QT_ARGS a.insts, a.one, a.ctls, a.bi, a.br, n, a.bound, what
-    if (what < 2) hipLaunchKernelGGL((k_op<T, SMALL, ONE, true, SELF>), g, t, 0, a.s, QT_ARGS);
-    else hipLaunchKernelGGL((k_op<T, SMALL, ONE, false, SELF>), g, t, 0, a.s, QT_ARGS);
+    if (what < 2) hipLaunchKernelGGL((k_op<T, SMALL, ONE, true, K>), g, t, 0, a.s, QT_ARGS);
+    else hipLaunchKernelGGL((k_op<T, SMALL, ONE, false, K>), g, t, 0, a.s, QT_ARGS);
 #undef QT_ARGS
 }
 
-template <typename T, bool SELF> static void op_launch(const CsrArgs &a, int what)
+template <typename T, int K> static void op_launch(const CsrArgs &a, int what)
 {
-    if (!a.use_one) op_launch_t<T, false, false, SELF>(a, what);
-    else if (a.one.d <= OP_SMALL_D) op_launch_t<T, true, true, SELF>(a, what);
-    else op_launch_t<T, false, true, SELF>(a, what);
+    if (!a.use_one) op_launch_t<T, false, false, K>(a, what);
+    else if (a.one.d <= OP_SMALL_D) op_launch_t<T, true, true, K>(a, what);
+    else op_launch_t<T, false, true, K>(a, what);
 }
 
-template <typename T, bool SELF> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
+template <typename T, int K> static void op_ctl(const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
 {
     const dim3 g(a.nblk), t(CSR_THREADS);
     const int n = a.xcd ? a.nblk : 0;
-    if (a.one.d <= OP_SMALL_D) hipLaunchKernelGGL((k_op_stage2_ctl<T, true, SELF>), g, t, 0, a.s, a.one, rd, wr, n);
-    else hipLaunchKernelGGL((k_op_stage2_ctl<T, false, SELF>), g, t, 0, a.s, a.one, rd, wr, n);
+    if (a.one.d <= OP_SMALL_D) hipLaunchKernelGGL((k_op_stage2_ctl<T, true, K>), g, t, 0, a.s, a.one, rd, wr, n);
+    else hipLaunchKernelGGL((k_op_stage2_ctl<T, false, K>), g, t, 0, a.s, a.one, rd, wr, n);
 }
 
+// K: the flags of OpForm a kernel serves (op_common); short column entries only without the self-jump mask.
 void op_spmv(const CsrLaunch &L, const CsrArgs &a, int first, int last)
 {
-    const auto launch = L.f64 ? (L.op_self ? op_launch<double, true> : op_launch<double, false>)
-                              : (L.op_self ? op_launch<float, true> : op_launch<float, false>);
+    const bool self = L.op_flags & OP_SELF, shorts = L.op_flags & OP_SHORT;
+    const auto launch = L.f64 ? (self ? op_launch<double, OP_SELF> : op_launch<double, 0>)
+                              : (self ? op_launch<float, OP_SELF> : shorts ? op_launch<float, OP_SHORT> : op_launch<float, 0>);
     for (int what = first; what <= last; ++what) launch(a, what);
 }
 
 void op_stage2_ctl(const CsrLaunch &L, const CsrArgs &a, const CsrCtl *rd, CsrCtl *wr)
 {
-    const auto launch = L.f64 ? (L.op_self ? op_ctl<double, true> : op_ctl<double, false>)
-                              : (L.op_self ? op_ctl<float, true> : op_ctl<float, false>);
+    const bool self = L.op_flags & OP_SELF, shorts = L.op_flags & OP_SHORT;
+    const auto launch = L.f64 ? (self ? op_ctl<double, OP_SELF> : op_ctl<double, 0>)
+                              : (self ? op_ctl<float, OP_SELF> : shorts ? op_ctl<float, OP_SHORT> : op_ctl<float, 0>);
     launch(a, rd, wr);
 }
 

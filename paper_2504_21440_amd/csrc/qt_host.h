@@ -120,6 +120,10 @@ bool csr_shape_supported(int lpr, int rg);
 // with 16-byte loads of 4-entry runs (built for 4x1, 8x1, 8x2 and 16x1).
 bool csr_shape_supported(int lpr, int rg, int keep);
 // One launch configuration of the CSR step kernels.
+// The operator-form kernel variant of problems with these flags: the self-jump mask where one needs it, short
+// column entries where all have them.
+inline int32_t op_common(int32_t a, int32_t b) { return ((a | b) & OP_SELF) | (a & b & OP_SHORT); }
+
 struct CsrLaunch {
     bool f64 = false;
     int lpr = 8, rg = 1, xcd = 0;  // tile shape and block order
@@ -135,7 +139,7 @@ struct CsrLaunch {
     const int32_t *bound = nullptr, *ibound = nullptr;
     const CsrInst *one_host = nullptr;           // host copy of the descriptor when ninst == 1
     bool op = false;  // every problem of the launch has operator tables: kernels_op.hip
-    bool op_self = false;  // and some problem's channels have diagonal entries
+    int32_t op_flags = 0;  // the kernel variant they take (op_common)
     bool td = false;  // some problem has a time-dependent Liouvillian: the SpMV kernels weight its terms
     // One problem with runs of 4 stored entries and no steady-state test: the step control
     // is folded into the next step's stage-2 launch (csr_launch_step).

@@ -20,26 +20,33 @@ constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
 //   diag [d]     A_ii
 //   lcol [w][d]  column of A's off-diagonal entry | column of C_c's entry << 16 (0xffff: none)
 //   aval [w][d]  A's values, state precision
-//   cval [w][d]  C_c's value, FP64 (a product of two is rounded once, as the assembled matrix rounds it)
+//   cval [w][d]  C_c's value over a factor f_c of the channel, FP64 (a product of two entries is rounded once, as
+//                the assembled matrix rounds it)
+//   cshort [w][d]  cval in FP32 (mixed precision; used where that is exact)
 //   rows [d]     records: columns of A [w], of the jumps [w] (-1: none), values of A [w] (state precision), of the
-//                jumps [w] (FP64)
+//                jumps times conj f_c [w] (FP64)
+// f_c is the channel's first entry, where that makes every cval exact in FP32 (a rate's root times entries +-1,
+// +-i, as spin operators have), else 1.
 // One allocation holds them, so that descriptors (kernel arguments of every CSR launch) stay short.
 struct OpForm {
     const void *mem;
     int32_t w;
-    int32_t self;  // 1: some C_c has an entry on its diagonal, so jumps reach the element itself
+    int32_t flags;
 };
+constexpr int32_t OP_SELF = 1;   // some C_c has an entry on its diagonal, so jumps reach the element itself
+constexpr int32_t OP_SHORT = 2;  // cshort is exact
 
 // Byte offsets of the tables (diag at 0) for state elements of es bytes, and the bytes of all.
 struct OpOffsets {
-    uint32_t lcol, aval, cval, rows, total;
+    uint32_t lcol, aval, cval, cshort, rows, total;
     __host__ __device__ OpOffsets(int d, int w, uint32_t es)
     {
         const uint32_t n = (uint32_t)w * (uint32_t)d;
         lcol = up((uint32_t)d * 16u);
         aval = lcol + up(n * 4u);
         cval = aval + up(n * es);
-        rows = cval + up(n * 16u);
+        cshort = cval + up(n * 16u);
+        rows = cshort + (es == 8 ? up(n * 8u) : 0u);
         total = rows + up((uint32_t)d * rec(w, es));
     }
     static __host__ __device__ uint32_t rec(int w, uint32_t es) { return (uint32_t)w * (8u + es + 16u); }  // bytes of a row's record

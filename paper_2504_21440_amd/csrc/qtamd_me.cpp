@@ -705,7 +705,8 @@ static CsrLaunch csr_args(const qt_me_plan *P, int k = 0)
     L.fused = folds_control(P, P->shape.keep);
     if (l.op) {
         L.op = true;
-        for (int32_t i : l.members) L.op_self = L.op_self || P->h_ci[i].op.self;
+        L.op_flags = P->h_ci[l.members[0]].op.flags;
+        for (int32_t i : l.members) L.op_flags = op_common(L.op_flags, P->h_ci[i].op.flags);
         L.xcd = 1;  // a problem's rows share an L2: 16 chains of L = 8 miss it half as often
         L.fused = folds_control(P, 2);
     }

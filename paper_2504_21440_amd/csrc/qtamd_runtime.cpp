@@ -526,7 +526,22 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
     w = std::max(4, (w + 1) & ~1);
     const size_t es = prec == QT_F64 ? 16 : 8, rec = OpOffsets::rec(w, (uint32_t)es);
     const OpOffsets o(d, w, (uint32_t)es);
-    bool self = false;
+    // the factor of each channel (qt_op.h)
+    int32_t flags = prec == QT_F64 ? 0 : OP_SHORT;
+    std::vector<cd> f(nc, cd(1.0, 0.0));
+    auto exact = [](cd u) { return (double)(float)u.real() == u.real() && (double)(float)u.imag() == u.imag(); };
+    for (int32_t c = 0; c < nc; ++c) {
+        if (cs[c].nnz() == 0) continue;
+        const cd f0 = cs[c].val[0];
+        bool ok = f0 != cd(0.0, 0.0);
+        for (int64_t p = 0; ok && p < cs[c].nnz(); ++p) {
+            const cd u = cs[c].val[p] / f0;
+            ok = exact(u) && u * f0 == cs[c].val[p];
+        }
+        if (ok) f[c] = f0;
+        else
+            for (const cd &v : cs[c].val) flags &= exact(v) ? ~0 : ~OP_SHORT;
+    }
     const size_t o_lc = o.lcol, o_av = o.aval, o_cv = o.cval, o_rec = o.rows, total = o.total;
     std::vector<char> h(total, 0);
     double2 *diag = (double2 *)h.data();
@@ -557,9 +572,12 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
             lc[(size_t)c * d + i] |= (int32_t)((uint32_t)(has ? rcc[c] : 0xffff) << 16);
             if (!has) continue;
             const cd v = cs[c].val[cs[c].ptr[i]];
-            ((double2 *)(h.data() + o_cv))[(size_t)c * d + i] = make_double2(v.real(), v.imag());
-            ((double2 *)(h.data() + rcv))[c] = make_double2(v.real(), v.imag());
-            self = self || rcc[c] == i;
+            const cd u = v / f[c], r = v * std::conj(f[c]);
+            ((double2 *)(h.data() + o_cv))[(size_t)c * d + i] = make_double2(u.real(), u.imag());
+            if (es == 8)
+                ((float2 *)(h.data() + o.cshort))[(size_t)c * d + i] = make_float2((float)u.real(), (float)u.imag());
+            ((double2 *)(h.data() + rcv))[c] = make_double2(r.real(), r.imag());
+            if (rcc[c] == i) flags |= OP_SELF;
         }
     }
     if (hipMalloc(&L->op_mem, total) != hipSuccess) {  // then the matrix kernels take the problem
@@ -571,7 +589,7 @@ static qt_status build_op_tables(const HCsr &A, const std::vector<HCsr> &cs, int
         return set_error(QT_EDEVICE, "upload operator tables");
     L->op.mem = L->op_mem;
     L->op.w = w;
-    L->op.self = self ? 1 : 0;
+    L->op.flags = flags;
     return QT_OK;
 }
 

@@ -88,7 +88,8 @@ struct Request {
     uint64_t ticket = 0;
     int32_t slot = -1;
     bool dense = false;
-    bool op = false, op_self = false;  // run by the operator-form kernels; a channel has diagonal entries
+    bool op = false;   // run by the operator-form kernels
+    int32_t op_flags = 0;
     int32_t res = -1;  // kernel class of a resident request (kernels_res.hip), -1: not one
     int32_t d = 0, nt = 0, ne = 0, np = 0;
     size_t off = 0, bytes = 0;
@@ -361,7 +362,7 @@ static qt_status server_submit(qt_server *S, const qt_me_problem *p, uint64_t *t
     R.dense = dense;
     R.res = rescls;
     R.op = op;
-    R.op_self = op && p->L->op.self;
+    R.op_flags = p->L->op.flags;
     R.d = d;
     R.nt = p->n_t;
     R.ne = p->n_e;
@@ -389,10 +390,10 @@ static void drop_graphs(qt_server::Lane &ln)
 
 // Uploads a lane's block table and control list and launches its epoch graph (capturing it on
 // first use of this grid size) on stream s.
-// op: run by the operator-form kernels; self: some of its problems' channels have diagonal entries.
+// op: run by the operator-form kernels, in the variant of `flags`.
 static qt_status launch_lane(qt_server *S, qt_server::Lane &ln, const std::vector<int32_t> &bi,
                              const std::vector<int32_t> &br, const std::vector<int32_t> &slots, int K, bool op,
-                             bool self, hipStream_t s)
+                             int32_t flags, hipStream_t s)
 {
     int grid = 256;
     while ((size_t)grid < bi.size()) grid *= 2;
@@ -404,7 +405,7 @@ static qt_status launch_lane(qt_server *S, qt_server::Lane &ln, const std::vecto
     QT_HIP(hipMemcpyAsync(ln.d_br, br.data(), br.size() * 4, hipMemcpyHostToDevice, s));
     QT_HIP(hipMemcpyAsync(ln.d_ilist, slots.data(), slots.size() * 4, hipMemcpyHostToDevice, s));
     QT_HIP(hipMemcpyAsync(ln.d_counts, ln.h_counts, sizeof(ln.h_counts), hipMemcpyHostToDevice, s));
-    const int key = grid + (self ? 1 : 0);  // a graph per grid size (a power of two) and kernel variant
+    const int key = grid + flags;  // a graph per grid size (a power of two, 256 or more) and kernel variant
     qt_server::EpochGraph &G = ln.graphs[key];
     if (!G.exec) {
         CsrLaunch L;
@@ -414,7 +415,7 @@ static qt_status launch_lane(qt_server *S, qt_server::Lane &ln, const std::vecto
         L.xcd = 0;
         L.keep = S->shape.keep;
         L.op = op;
-        L.op_self = self;
+        L.op_flags = flags;
         L.nblk = grid;               // blocks past the live count return at once
         L.ninst = S->cfg.max_slots;  // likewise for the control list
         L.ilist = ln.d_ilist;
@@ -454,12 +455,12 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     const int K = std::max(1, S->cfg.steps_per_epoch);
     // ---- CSR slots: one block table per lane ----
     std::vector<int32_t> bi[N_LANES], br[N_LANES], csr_slots[N_LANES];
-    bool op_self = false;
+    int32_t op_flags = -1;  // of the operator-form lane's requests
     const int rpb = csr_rows_per_block(S->shape.lpr, S->shape.rg);
     for (uint64_t tk : S->active) {
         Request &R = S->reqs[tk];
         if (R.dense || R.res >= 0) continue;
-        op_self = op_self || R.op_self;
+        if (R.op) op_flags = op_flags < 0 ? R.op_flags : op_common(op_flags, R.op_flags);
         const int l = R.op ? 2 : (int64_t)R.d * R.d <= SMALL_LANE_ROWS ? 1 : 0;
         for (int32_t b = 0; b < R.nblocks; ++b) {
             bi[l].push_back(R.slot);
@@ -514,7 +515,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
     if (!bi[0].empty() || !bi[2].empty()) {
         qt_status st = QT_OK;
         for (int l : {0, 2})
-            if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l == 2, l == 2 && op_self, s);
+            if (!st && !bi[l].empty()) st = launch_lane(S, S->lanes[l], bi[l], br[l], csr_slots[l], K, l == 2, l == 2 ? op_flags : 0, s);
         if (st) {
             if (ev) (void)hipEventDestroy(ev);
             return st;
@@ -536,7 +537,7 @@ static qt_status server_step(qt_server *S, int32_t *n_active, int32_t *n_finishe
             for (size_t k = 0; k < rruns.size() && !st; ++k)
                 st = res_launch(rruns[k].cls, f64, S->d_rinst, S->d_rctl, S->d_order + rruns[k].start, rruns[k].count,
                                 K, 0, nfree ? ctx->pool[nb + (int)k % nfree] : sa);
-            if (!st && !bi[1].empty()) st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, false, false, sa);
+            if (!st && !bi[1].empty()) st = launch_lane(S, S->lanes[1], bi[1], br[1], csr_slots[1], K, false, 0, sa);
             if (!st && !bi[1].empty())
                 e = hipMemcpyAsync(S->h_cctl, S->d_cctl, sizeof(CsrCtl) * S->cfg.max_slots, hipMemcpyDeviceToHost, sa);
             for (int b = 0; b < nfree && e == hipSuccess; ++b) e = hipStreamSynchronize(ctx->pool[nb + b]);

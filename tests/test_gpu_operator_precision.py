@@ -69,3 +69,58 @@ def test_channels_on_and_off_the_diagonal(ctx, d, prec):
     ex = qt.mesolve(ctx, L, psi, tl, e, options=qt.opts(precision=prec, abstol=1e-8, reltol=1e-6))[0]
     L.close()
     assert np.abs(ex - ref).max() <= (1e-9 if prec == qt.F64 else 1e-4), np.abs(ex - ref).max()
+
+
+def _unit_channels(d, seed):
+    """Channels whose entries are a complex factor times +-1 and +-i (short column entries), one of them on the
+    diagonal."""
+    g = np.random.default_rng(seed)
+    v = 0.4 * g.normal(size=d - 1)
+    H = sp.diags([g.normal(size=d), v, v], [0, 1, -1], format="csr").astype(complex)
+    cs = []
+    for s, f in [(1, np.sqrt(0.2)), (2, np.sqrt(0.3) * np.exp(0.7j)), (d // 2, 0.3j)]:
+        cs.append(sp.csr_matrix(sp.diags(f * g.choice([1, -1, 1j, -1j], size=d - s), s, shape=(d, d))))
+    psi = g.normal(size=d) + 1j * g.normal(size=d)
+    return H, cs, psi / np.linalg.norm(psi)
+
+
+@pytest.mark.parametrize("prec", [qt.F64, qt.MIXED])
+def test_kernel_variants_in_one_launch(ctx, prec):
+    """Channels with short column entries, without, and with diagonal entries: alone, all in one plan, and two
+    kinds in another, bitwise the same; the short ones against the oracle."""
+    print(f"[gpu] operator precision variants prec={prec}", flush=True)
+    o = qt.opts(precision=prec)
+    tl = np.linspace(0.0, 0.3, 4)
+    probs = []
+
+    def add(H, cs, psi):
+        d = H.shape[0]
+        e = [sp.diags(np.linspace(0, 1, d)).astype(complex).tocsr()]
+        probs.append((qt.Liouvillian(ctx, H, cs, qt.FORM_CSR, prec), psi, tl, e))
+        return H, cs, psi, tl, e
+
+    short = [add(*_unit_channels(d, d)) for d in (130, 258)]
+    g = np.random.default_rng(3)
+    for d in (140, 300):
+        H, cs, psi = _unit_channels(d, d)
+        add(H, [sp.csr_matrix(sp.diags(0.4 * g.normal(size=d - 1), 1, shape=(d, d)).astype(complex))], psi)
+        add(H, cs[:1] + [sp.csr_matrix(sp.diags(0.4 * g.normal(size=d)).astype(complex))], psi)
+    lone = []
+    for p in probs:
+        q = qt.MePlan(ctx, [p], o)
+        q.run()
+        lone.append(q.result(0, want_final=True))
+        q.close()
+    for k, s in enumerate(short):
+        ref = oracle.mesolve(*s)[0]
+        assert np.abs(lone[k][0] - ref).max() <= (1e-9 if prec == qt.F64 else 1e-4)
+    for pick in (range(len(probs)), [0, 2], [1, 3], [0, 1]):
+        plan = qt.MePlan(ctx, [probs[i] for i in pick], o)
+        plan.run()
+        for k, i in enumerate(pick):
+            got = plan.result(k, want_final=True)
+            np.testing.assert_array_equal(got[0], lone[i][0])
+            np.testing.assert_array_equal(got[2], lone[i][2])
+        plan.close()
+    for p in probs:
+        p[0].close()
