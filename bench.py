@@ -1010,7 +1010,7 @@ def main():
     tf = 8.0 * mixed["nnz"] * mixed["rhs_per_s"] / 1e12
     rl = {"bound": "latency", "achieved": tf, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
           "frac": tf / FP32_VECTOR_PEAK_TFLOPS,
-          "kernel": "k_op<float,true,true,false> (operator form, upper triangle), L=8 chain, one launch = one stage",
+          "kernel": "k_op<float,true,true,false,OP_SHORT> (operator form, upper triangle), L=8 chain, one launch = one stage",
           "regime": "us_per_rhs over the whole solve, launches and step control included; a stage is one launch of "
                     "160 workgroups, bound by the latency of a wave",
           "us_per_rhs": 1e6 / mixed["rhs_per_s"], "matrix_stage_kernel": matrix,

@@ -173,8 +173,9 @@ qt_status qt_liouv_info(const qt_liouv *L, int32_t *d, int64_t *nnz, int64_t *by
 /* Device bytes the Liouvillian holds until qt_liouv_destroy: CSR row pointers, columns and values
  * (and the coefficient tables of a time-dependent one), or the dense operators.  A served request
  * is charged this plus its own state (qt_server_footprint).  A constant CSR Liouvillian whose
- * operators have few entries per row keeps them beside it (at most 12 entries per row of each of two
- * d x d tables, twice), which is not counted. */
+ * operators have few entries per row keeps tables of them beside it (at most 12 entries per row of the
+ * effective Hamiltonian and of the collapse operators, in two layouts: under 1,000 bytes per dimension of
+ * the Hilbert space), which is not counted. */
 qt_status qt_liouv_footprint(const qt_liouv *L, size_t *bytes);
 /* Copies the assembled CSR back to the host (values widened to complex128, row padding left out).
  * indptr: d*d + 1, indices and values: nnz from qt_liouv_info.  CSR form only. */

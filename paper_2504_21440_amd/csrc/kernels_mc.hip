@@ -62,8 +62,11 @@ template <typename T, int R, bool TD, int OCC> static const void *mc_fn()
 
 // Ensembles of at least this many complex64 trajectories with 2, 4 or 8 rows per thread take the
 // variant held to 3 waves per SIMD (2 at 8 rows): more trajectories in flight outweigh the spilled
-// registers (measured on dissipative chains of L = 9, 10, 11: +34%, +20% and +61% trajectories/s
-// at 2,048 trajectories); a lone trajectory runs 10-20% slower there, so it keeps the other one.
+// registers; a lone trajectory runs 10-20% slower there, so it keeps the other one.  Constant matrices of up
+// to 12 entries per row are held in registers instead (kernels_mc_reg.hip).  What is left, trajectories/s of
+// 2,047 (unconstrained) and of 2,048: constant, 15 entries per row, d = 512 680,000 and 689,000, d = 1,024
+// 258,000 and 362,000, d = 2,048 85,200 and 130,600; driven chains (time-dependent) of L = 9 192,000 and
+// 196,000, L = 10 64,000 and 81,700, L = 11 15,300 and 26,000.
 constexpr int64_t MC_DENSE_ENSEMBLE = 2048;
 static bool mc_occ3(const McParams &p, bool f64)
 {

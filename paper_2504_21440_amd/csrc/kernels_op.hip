@@ -14,8 +14,8 @@
 // What bounds it: one chain of L = 8 (160 workgroups) the latency of a wave, kernel by kernel -- 4.8 us a stage in
 // complex64, of which the launch is about 2 -- so there a wave takes one row, the descriptor, the control record
 // and the column's entries are requested together, and every source before the first sum; with descriptor
-// words read where they are used it took 5.0 us (a solve 4.29 ms against 4.14, in complex128 4.05 against
-// 3.66 ms), with two rows 6.1 us.
+// words read where they are used it took 5.0 us (a solve to t = 10, 126 steps, 4.29 ms against 4.14, in complex128
+// 4.05 against 3.66 ms), with two rows 6.1 us.
 // L = 10 (complex128) the vector L1: 30 sources and 20 table words per element at 4 lanes a cycle are 12 us,
 // beside 130 MB of state vectors from the L2s and the MALL; 28 us a stage (118 us for the matrix kernels, which
 // stream 531 MB; 40 us without the Hermitian halving).  Two rows a wave read each column entry for two
@@ -25,8 +25,9 @@
 // Precision: as in the assembled matrix, the factor of the element itself (the diagonals of A and the jumps that
 // start from the element) is summed in FP64 and rounded once, and so is each product of two C entries.  With
 // products of rounded C entries a diagonal channel's decay and jump, which cancel in the matrix, left 2e-7 of
-// the rate: after t = 100 with C = sqrt(0.1) n (d = 160) populations had drifted by 1e-4.  Everything else of a
-// step -- stage combinations, error partials, control, expectation values -- is that of kernels_csr.hip, on
+// the rate: after t = 20 with C = sqrt(0.1) n (d = 160) populations were off by 7e-4 of the largest (now 3e-8, as
+// with the matrix).  The derivative of a diagonal element is real, so the state stays exactly Hermitian.
+// Everything else of a step -- stage combinations, error partials, control, expectation values -- is that of kernels_csr.hip, on
 // the same descriptors, with op_blocks(d) partials a problem.
 #include <type_traits>
 

@@ -14,18 +14,21 @@
 // each (value and 16-bit LDS offset) in registers, so a right-hand side is W LDS gathers per element
 // and no memory traffic: what bounds it is LDS gathers and multiply-add issue for the large
 // classes and the latency of one gather-accumulate-write-barrier round for the small ones.
-// LDS holds two d x (d | 1) matrices, so one barrier separates consecutive stages; the odd row stride
-// keeps the mirror writes (a column of the matrix) on distinct banks.
+// LDS holds two matrices, so one barrier separates consecutive stages; their row stride is that of the
+// largest dimension of the kernel class, made odd, which keeps the mirror writes (a column of the matrix) on
+// distinct banks.
 //
 // A step is six rounds.  For a constant L, k2 = L (y + a21 h k1) = k1 + a21 h (L k1) with k1 = k7 of
 // the step before, so k7 is written to LDS as soon as it is known, and the product L k7 is formed while
 // the step control (FP64 logarithm, exponential, square root) runs: the control's latency is hidden
 // behind the gathers, and a rejection (rare) forms L k1 again.
 //
-// Measured (MI355X, lone driven cavities, us a step of six right-hand sides, save times included; before:
-// the staged CSR kernels below d = 55 in FP64, the matrix-core kernel for mixed precision):
-//   d = 20 FP64 3.6 (21.2 before), d = 44 FP64 5.5, d = 60 mixed 8.9, d = 80 mixed 15.1 (120 before).
-// A sweep of 64 cavities of cutoff 10 to 80 over t = 1 went from 75 to 11 ms.  With 16-bit offsets in
+// Measured (MI355X, lone driven cavities, us a step of six right-hand sides in solves of 20 to 130 steps, start and
+// 20 save times included; before: the staged CSR kernels below d = 55 in FP64, the matrix-core kernel for mixed
+// precision):
+//   d = 20 FP64 3.6 (21.2 before; 2.8 over 783 steps), d = 44 FP64 5.6, d = 60 mixed 8.9, d = 80 mixed 15.2 (120
+//   before).
+// A sweep of 64 cavities of cutoff 10 to 80 over t = 1 went from 71 to 8.4 ms.  With 16-bit offsets in
 // registers instead of the band's constant ones the d = 80 step took 23.4 us (spilled registers).
 //
 // FP64, as in the other solvers: step control, error norm (an element above the diagonal counts for

@@ -23,6 +23,11 @@
 // and the compiler saved registers in that branch's join block ahead of the instruction that restores the
 // execution mask.  The angle is never large, so the saves ran for no lane: one was the step counter, and
 // the step loop of a complex128 ket of 1,025 entries did not end.
+//
+// What bounds it: the round trips of the operator reads from L2 and 6 + 3 m barriers a step (m processes).  Two
+// measured operators, 400 steps, before and after the processes became a loop: 500 trajectories of n = 1,024
+// (master equation, complex64) 7.00 and 6.27 ms, of n = 256 in complex128 3.37 and 2.57 ms; 500 kets of 1,024
+// in complex64 6.44 and 5.79 ms; 200 in complex128 5.54 and 5.53 ms.
 #include <algorithm>
 
 #include "qt_common.h"

@@ -1,8 +1,8 @@
 // kernels_sde_reg.hip -- stochastic trajectories with one measured operator, operators in registers.
 //
 // The scheme, the draws and the outputs are those of kernels_sde.hip (its header has the formulas).  That
-// kernel reads A and B from L2 at every product, evaluates every Wiener increment in all threads (an FP64
-// logarithm, square root, sine and cosine a step) and passes 12 barriers a step.  With one measured
+// kernel reads A and B from L2 at every product, draws increments (an FP64 logarithm, square root, sine and cosine)
+// at every step and passes nine barriers a step with one measured operator.  With one measured
 // operator and few entries per row (the Lindbladian of a cavity and a qubit has 5, its measured operator
 // 2), here
 //   * a thread keeps the entries of its rows in registers, as values and 16-bit LDS byte offsets;

@@ -6,10 +6,24 @@
 namespace qt {
 
 constexpr int OP_MAX_W = 12;  // off-diagonal entries per row of A, and collapse operators
-// Below OP_MIN_D the matrix kernels' shorter chain of loads is faster for one problem: a chain of L = 7
-// (d = 128) took 1.97 ms a solve in operator form against 1.62 ms, L = 8 1.97 ms against 2.51 ms.  (From 32 on a
-// problem has no more workgroups (op_blocks) than their default shape has, which is what partial sums and
+// Below OP_MIN_D the matrix kernels' shorter chain of loads is faster for one problem: a chain of L = 7 (d = 128)
+// took 1.97 ms in operator form against 1.62 ms to t = 2 (rtol 1e-5), L = 8 1.97 ms against 2.51 ms.  (From
+// 32 on a problem has no more workgroups (op_blocks) than their default shape has, which is what partial sums and
 // block tables are sized for.)  Up to OP_MAX_D a state's byte offsets have 32 bits.
+//
+// Above it the rule looks at batches as much as at lone problems, since a problem's solver may not depend on what it
+// runs with.  Matrix kernels and operator form, us a step, banded problems of w off-diagonal entries per row and nc
+// channels, complex64 (complex128 is more favourable by 5 to 20%):
+//                       one problem                              16 problems
+//             w 2, nc 1   w 8, nc 8   w 12, nc 12     w 2, nc 1   w 8, nc 8   w 12, nc 12
+//   d = 130   30  30      32  35      35  41          86  69      152  90     170  119
+//   d = 160   32  32      38  37      36  39          114 81      193  103    211  117
+//   d = 192   33  30      41  37      45  41          146 80      226  107    266  126
+//   d = 257   43  48      60  53      67  62          291 144     405  175    483  214
+//   d = 320   53  40      87  53      99  62          347 140     596  186    737  231
+//   d = 512   97  51      173 63      192 74          939 305     1477 375    1795 459
+// So one problem of d up to 160 with wide operators pays up to 15%, and one just above d = 256, where a wave takes
+// two rows, up to 10% if its operators are narrow; batches gain 1.2 to 4 times everywhere.
 constexpr int OP_MIN_D = 129, OP_MAX_D = 8192;
 
 // L(rho) = A rho + rho A^dag + sum_c C_c rho C_c^dag from d x d tables (device pointers; w = 0: none).
@@ -54,8 +68,10 @@ struct OpOffsets {
 };
 
 // Rows one wave serves: fixed by the dimension, so that a problem's sums do not depend on the plan.  Up to
-// d = 256 one problem does not fill the chip and the latency of a wave counts (one chain of L = 8: 4.3 ms a solve
-// with one row, 5.4 ms with two); above, the vector L1 (L = 10, complex128: 14.2 ms and 12.4 ms).
+// d = 256 one problem does not fill the chip and the latency of a wave counts (one chain of L = 8: 4.3 ms to t = 10
+// with one row, 5.4 ms with two); above, the vector L1 (L = 10, complex128: 14.2 ms and 12.4 ms).  In between one
+// row suits one problem, two a batch (d = 320, w = 8, complex64: one problem 38 and 53 us a step, sixteen 212
+// and 186; d = 257: 37 and 53, 204 and 175).
 constexpr int OP_ROWS = 2, OP_ROWS_SMALL = 1, OP_SMALL_D = 256;
 __host__ __device__ inline int op_rows(int d) { return d > OP_SMALL_D ? OP_ROWS : OP_ROWS_SMALL; }
 

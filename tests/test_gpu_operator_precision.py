@@ -3,8 +3,8 @@
 Dephasing C = sqrt(g) n of a coherent state leaves every population as it is: the decay of rho_ii and the jump
 into it cancel.  They cancel in FP64 before the one rounding of the element's factor, so k_ii is exactly 0
 and a population only sees the rounding of the trace's renormalisation: 1e-6 of itself in mixed precision,
-1e-12 in FP64.  (With rounded operator entries 2e-7 of the rate 0.1 n^2 was left: after t = 20 populations had
-moved by 1e-5 and <n> by 1e-4 and more.)  The second channel set has rows on and off the diagonal in one operator;
+1e-12 in FP64.  (With rounded operator entries 2e-7 of the rate 0.1 n^2 was left: after t = 20 populations were
+off by 7e-4 of the largest.)  The second channel set has rows on and off the diagonal in one operator;
 there the oracle's integrator at the same tolerances is the reference (1e-9 in FP64, 1e-4 in mixed precision)."""
 from math import lgamma
 
